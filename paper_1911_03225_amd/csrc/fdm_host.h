@@ -35,6 +35,9 @@ double smax_uniform(const fdm_transport_desc &d);
 // (the unit-speed step when smax = 0).
 float step_dt(const fdm_transport_desc &d, double smax);
 
+// How the FP64 update divides by the spacings (SPACING_*).
+int spacing_kind(double dx, double dy);
+
 // The device view of one instance with step dt and stage buffer (w11, w12);
 // the state pointers and the tiling are left unset.
 void fill_inst(InstDev &I, const fdm_transport_desc &d, float dt, void *w11, void *w12);

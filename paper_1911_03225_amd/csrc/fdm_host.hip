@@ -143,6 +143,15 @@ float step_dt(const fdm_transport_desc &d, double smax)
     return round_down_float(smax > 0.0 ? d.cfl * h / smax : d.cfl * h);
 }
 
+int spacing_kind(double dx, double dy)
+{
+    int ex = 0, ey = 0;
+    const double mx = std::frexp(dx, &ex), my = std::frexp(dy, &ey);
+    if (std::max(std::abs(ex), std::abs(ey)) <= 1000 && mx == 0.5 && my == 0.5) return SPACING_POW2;
+    if (std::max(std::abs(ex), std::abs(ey)) < 100) return SPACING_SHARED;
+    return SPACING_DIVIDE;
+}
+
 void fill_inst(InstDev &I, const fdm_transport_desc &d, float dt, void *w11, void *w12)
 {
     std::memset(&I, 0, sizeof(I));
@@ -157,6 +166,9 @@ void fill_inst(InstDev &I, const fdm_transport_desc &d, float dt, void *w11, voi
     I.dtd = (double)dt;
     I.dxd = d.dx;
     I.dyd = d.dy;
+    I.rdxd = 1.0 / d.dx;
+    I.rdyd = 1.0 / d.dy;
+    I.spacing_kind = spacing_kind(d.dx, d.dy);
     I.cxd = (double)dt / d.dx;
     I.cyd = (double)dt / d.dy;
     I.thetad = d.limiter == FDM_LIMITER_MINMOD ? 1.0 : d.limiter == FDM_LIMITER_MC ? 2.0 : d.theta;

@@ -176,6 +176,11 @@ __device__ __forceinline__ void coupled_slip_block(const SlipArgs &a, double2 *l
     }
 }
 
+// How d / dx and d / dy may be taken in the FP64 update: by the reciprocals
+// alone (both spacings a power of two, both reciprocals normal), by the
+// reciprocals and one correction (both in [2^-100, 2^100]), or by division.
+enum : int { SPACING_DIVIDE = 0, SPACING_SHARED = 1, SPACING_POW2 = 2 };
+
 // Device view of one transport instance.
 struct InstDev {
     void *a11, *a12;         // state, caller-owned (float, or double in PREC_FP64)
@@ -192,6 +197,8 @@ struct InstDev {
     int64_t tile_begin;      // first global tile of this instance (batched)
     double cxd, cyd, thetad; // the same coefficients for FP64 arithmetic
     double dtd, dxd, dyd;    // step and spacings (FP64 update in definition form)
+    double rdxd, rdyd;       // 1/dx, 1/dy, rounded to nearest
+    int32_t spacing_kind, pad3;   // how the FP64 update divides by them
     double *hsum;            // per-tile sums of Hhat (coupled runs) or nullptr
     // Coupled runs: the step comes from the velocity law's max |v0|
     // partials, reduced by every wave of the stage kernels (so no launch

@@ -51,17 +51,20 @@ __device__ __forceinline__ float from_right(float v)
 
 __device__ __forceinline__ double from_left(double v)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, false);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x138, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x138, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
 }
 
 __device__ __forceinline__ double from_right(double v)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, false);
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x130, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x130, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
 }
+
+// every active lane's condition (a scalar compare of the wave's mask)
+__device__ __forceinline__ bool wave_all(bool c) { return __builtin_amdgcn_ballot_w64(!c) == 0; }
 
 // ------------------------------------------------------- arithmetic types
 //
@@ -395,6 +398,110 @@ __device__ __forceinline__ double numerical_hamiltonian_ieee(double pxm, double 
     }
 }
 
+// FP64 modes, H = v0 |p|: numerical_hamiltonian_ieee's value from about 0.4
+// of the instructions, the same bits wherever the caller's and the returned
+// conditions hold.
+//
+// The FP64 stages are bound by VALU issue: the definition's form spends 14
+// divisions (11 instructions each) and 4 square roots (17) per node.  Here
+//   * the running max of v0 p^s / |p| over t is the quotient at the smaller
+//     |p| (rounding is monotone: fl(n / r) does not grow with r, nor does
+//     fl(sqrt) shrink with its argument), so 4 speed quotients are left of 8;
+//     a |p| of 0 belongs to p^s = 0 and its quotient is 0 whatever divides;
+//   * quotients by the same divisor share its reciprocal, which for |p| comes
+//     out of the square root's own iteration, and the operands are known to
+//     lie where the scaling steps of the IEEE sequences do nothing: a
+//     division is a product and one fused correction.
+// Ranges.  The caller sees to it that every density of the stencil is 0 or
+// in [2^-250, 2^370] (edge_in_range).  Then slopes are 0 or at least
+// 2^-303, face values are 0 or at least one unit in the last place of an
+// operand, 2^-357, so the squares stay in [2^-714, 2^743] and the roots and
+// speed quotients (v0 is a float) are normal with exact remainders.  The
+// products a+ a- and b+ b- are 0 or at least 2^-900, checked here: then
+// weights and viscosities are normal and their remainders exact too.
+// Measured: see edge_in_range.
+
+// a / b from a reciprocal y of b
+__device__ __forceinline__ double shared_quot(double a, double b, double y)
+{
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-b, q, a), y, q);
+}
+
+// sqrt(x) for x = 0 or x in [2^-760, 2^762], by Goldschmidt's iteration from
+// the hardware estimate and two corrections (the bound on the estimate makes
+// sqrt(0) = 0); h comes out near 1 / (2 sqrt(x)).
+__device__ __forceinline__ double root_in_range(double x, double &h)
+{
+    const double y = __builtin_fmin(__builtin_amdgcn_rsq(x), 0x1p450);
+    double g = x * y;
+    h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+}
+
+// One axis: projection weights and viscosity from the one-sided speeds; true
+// where the shared reciprocal gives their exact rounding.  Where nothing
+// moves the bound makes the reciprocal finite, so the quotients come out 0.
+__device__ __forceinline__ bool axis_shared(double am, double ap, double &wm, double &wp, double &visc)
+{
+    const double d = ap - am, prod = ap * am;
+    double y = __builtin_amdgcn_rcp(__builtin_fmax(d, 0x1p-1000));
+    y = __builtin_fma(y, __builtin_fma(-d, y, 1.0), y);
+    y = __builtin_fma(y, __builtin_fma(-d, y, 1.0), y);
+    const double still = d > 0.0 ? 0.0 : 0.5;
+    wm = shared_quot(ap, d, y) + still;
+    wp = shared_quot(-am, d, y) + still;
+    visc = shared_quot(prod, d, y);
+    return (prod == 0.0) | (prod <= -0x1p-900);
+}
+
+__device__ __forceinline__ bool numerical_hamiltonian_shared(double pxm, double pxp, double pym, double pyp, double v0,
+                                                             double &hhat)
+{
+    const double xm2 = pxm * pxm, xp2 = pxp * pxp, ym2 = pym * pym, yp2 = pyp * pyp;
+    double h00, h01, h10, h11;
+    const double r00 = root_in_range(xm2 + ym2, h00), r01 = root_in_range(xm2 + yp2, h01);
+    const double r10 = root_in_range(xp2 + ym2, h10), r11 = root_in_range(xp2 + yp2, h11);
+    // v0 p / |p| at the smaller |p| of the face value's two corners; 2 h is
+    // its reciprocal to a unit in the last place, then one Newton step
+    auto speed = [&](double p, double ra, double rb, double ha, double hb) {
+        const double r = __builtin_fmin(ra, rb), y0 = 2.0 * __builtin_fmax(ha, hb);
+        return shared_quot(v0 * p, r, __builtin_fma(y0, __builtin_fma(-r, y0, 1.0), y0));
+    };
+    const double hxm = speed(pxm, r00, r01, h00, h01), hxp = speed(pxp, r10, r11, h10, h11);
+    const double hym = speed(pym, r00, r10, h00, h10), hyp = speed(pyp, r01, r11, h01, h11);
+    const double ap = __builtin_fmax(__builtin_fmax(hxm, hxp), 0.0), am = __builtin_fmin(__builtin_fmin(hxm, hxp), 0.0);
+    const double bp = __builtin_fmax(__builtin_fmax(hym, hyp), 0.0), bm = __builtin_fmin(__builtin_fmin(hym, hyp), 0.0);
+    double wxm, wxp, wym, wyp, visc_x, visc_y;
+    bool ok = axis_shared(am, ap, wxm, wxp, visc_x);
+    ok &= axis_shared(bm, bp, wym, wyp, visc_y);
+    double s = 0.0 + wxm * wym * (v0 * r00);   // as the definition sums: +0 where all vanish
+    s += wxm * wyp * (v0 * r01);
+    s += wxp * wym * (v0 * r10);
+    s += wxp * wyp * (v0 * r11);
+    hhat = s + (visc_x * (pxp - pxm) + visc_y * (pyp - pym));
+    return ok & (fabs(v0) < __builtin_inf());
+}
+
+// Whether a density lies where the shared evaluation above is exact: any
+// finite float, or a double that is 0 or of magnitude in [2^-250, 2^370)
+// (compared by its exponent).  A wave takes the definition's form for a row
+// where a lane's stencil is outside (the far tail of a front, below 1e-75).
+// Measured, 4096^2 with a celerity field, float64 state, both Heun stages:
+// 353 us a step against 512 us with the definition's form everywhere (float32
+// state, 1009 x 757, midpoint: 25.9 against 40.1 us).
+__device__ __forceinline__ bool edge_in_range(float w) { return fabsf(w) < __builtin_inff(); }
+__device__ __forceinline__ bool edge_in_range(double w)
+{
+    constexpr uint32_t lo = (1023u - 250u) << 21, hi = (1023u + 370u) << 21;
+    const uint32_t e = ((uint32_t)__double2hiint(w) << 1) - lo;
+    return (e < hi - lo) | (w == 0.0);
+}
+
 // Fully discrete scheme (sec. 3.2.3), float.  With the separable quadratic
 // interpolant the value over phi_jk at the corner (x_j + a^s dt, y_k + b^t dt)
 // is X_s + Y_t, X_s = dt a^s (p_x^s + a^s dt sx^s / (2 dx)), and its slope is
@@ -599,6 +706,27 @@ __device__ __forceinline__ void put(RowRef<double> row, uint32_t off, double v)
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), row.r, (int)off, 0, 0);
 }
 
+// FP64 update: d / spacing.  A power of two divides exactly by its
+// reciprocal; other spacings share theirs (rounded to nearest by the host)
+// for differences that are 0 or at least 2^-900, and divide where a lane's
+// is not.  spacing_kind is uniform over the launch.
+__device__ __forceinline__ void divide_spacings(double &dx, double &dy, const InstDev &I)
+{
+    if (I.spacing_kind == SPACING_POW2) {
+        dx *= I.rdxd;
+        dy *= I.rdyd;
+        return;
+    }
+    const bool ok = ((dx == 0.0) | (fabs(dx) >= 0x1p-900)) & ((dy == 0.0) | (fabs(dy) >= 0x1p-900));
+    if (I.spacing_kind == SPACING_SHARED && wave_all(ok)) {
+        dx = shared_quot(dx, I.dxd, I.rdxd);
+        dy = shared_quot(dy, I.dyd, I.rdyd);
+    } else {
+        dx /= I.dxd;
+        dy /= I.dyd;
+    }
+}
+
 template <int P> struct Phase {
     static constexpr int value = P;
 };
@@ -700,6 +828,13 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
     y[0] = at(row_ptr<S>(s11, k, nx), off);
     sl[1] = limited_slope<LK>(ym2, R(y[7]), R(y[0]), theta);   // slope at edge k0-1/2
     hh[1] = R(0);
+    // FP64: which of the last rows of alpha_11 hold values out of range
+    int y_out = 0;
+    if constexpr (kF64 && !kFD && VH == VK_LAW) {
+        if (!wave_all(edge_in_range(S(ym2)))) y_out |= 4;
+        if (!wave_all(edge_in_range(y[7]))) y_out |= 2;
+        if (!wave_all(edge_in_range(y[0]))) y_out |= 1;
+    }
     // float: the carried y difference of the first row and its scaled form
     float ydm = float(R(y[0]) - R(y[7]));
     float ydms = LK == LK_SUPERBEE ? 2.0f * ydm : float(theta) * ydm;
@@ -780,7 +915,15 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
             else
                 hv = fd_hamiltonian<VH>(pxm, pxp, pym, pyp, sxm, sx, -sl[hp], -s0, v0, V1, V2, cx, cy);
         } else if constexpr (kF64) {
-            hv = numerical_hamiltonian_ieee<VH>(pxm, pxp, pym, pyp, v0, V1, V2);
+            if constexpr (VH == VK_PRESCRIBED) {
+                hv = numerical_hamiltonian_ieee<VH>(pxm, pxp, pym, pyp, v0, V1, V2);
+            } else {
+                // rows k-2 .. k+1 of alpha_11 and row k of alpha_12 are the stencil
+                y_out = (y_out << 1 | (wave_all(edge_in_range(y[(p + 1) & 7])) ? 0 : 1)) & 15;
+                const bool ok = numerical_hamiltonian_shared(pxm, pxp, pym, pyp, v0, hv);
+                if (y_out != 0 || !wave_all(ok & edge_in_range(wx_[c])))
+                    hv = numerical_hamiltonian_ieee<VH>(pxm, pxp, pym, pyp, v0, V1, V2);
+            }
         } else {
             hv = numerical_hamiltonian<VH>(pxm, pxp, pym, pyp, v0, V1, V2);
         }
@@ -789,21 +932,23 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
         hh[h] = hv;
         if constexpr (HSUM) hacc += (out_col && it < nrows) ? hv : R(0);
 
+        R dhx = hr - hv, dhy = hv - hprev;
+        if constexpr (kF64) divide_spacings(dhx, dhy, I);
         {   // x-edge (j+1/2, k): d(alpha_12)/dt = -(Hhat_{j+1} - Hhat_j)/dx; not on the extra row
             R nv;
             const R from = MODE == MODE_MID2 ? b12 : wx;   // the state the stage adds to
-            if constexpr (kF64 && kFD) nv = from + (hr - hv) / I.dxd;   // differences of the increments
-            else if constexpr (kF64) nv = from + I.dtd * (-(hr - hv) / I.dxd);
-            else nv = madd(-cx, hr - hv, from);
+            if constexpr (kF64 && kFD) nv = from + dhx;   // differences of the increments
+            else if constexpr (kF64) nv = from + I.dtd * -dhx;
+            else nv = madd(-cx, dhx, from);
             if constexpr (MODE == MODE_HEUN2) nv = madd(R(0.5), b12, R(0.5) * nv);
             put(row_ptr<S>(d12, k, nx, it < nrows), off_st, S(nv));
         }
         {   // y-edge (j, k-1/2): d(alpha_11)/dt = (Hhat_k - Hhat_{k-1})/dy; from the second row on
             R nv;
             const R from = MODE == MODE_MID2 ? b11 : ym1;
-            if constexpr (kF64 && kFD) nv = from - (hv - hprev) / I.dyd;
-            else if constexpr (kF64) nv = from + I.dtd * ((hv - hprev) / I.dyd);
-            else nv = madd(cy, hv - hprev, from);
+            if constexpr (kF64 && kFD) nv = from - dhy;
+            else if constexpr (kF64) nv = from + I.dtd * dhy;
+            else nv = madd(cy, dhy, from);
             if constexpr (MODE == MODE_HEUN2) nv = madd(R(0.5), b11, R(0.5) * nv);
             put(row_ptr<S>(d11, kprev, nx, it > 0), off_st, S(nv));
         }

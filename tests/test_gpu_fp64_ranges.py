@@ -1,0 +1,76 @@
+"""FP64 modes where the shared-reciprocal evaluation of the numerical
+Hamiltonian starts and stops to apply: densities at the ends of its range,
+below it, zero beside them, and mixed; celerities that vanish; spacings that
+are a power of two, another value, and outside the range of the shared
+reciprocal.  The float64 state has to equal the FP64 oracle bit for bit
+(both evaluate the same IEEE operations), so there is no tolerance."""
+import numpy as np
+import pytest
+
+from gpu_util import oracle_problem, to_dev
+from paper_1911_03225_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fdm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1911_03225_amd import fdm as F
+    F.load_library()
+    return F
+
+
+def _run(fdm, oracle, a11, a12, steps, v0_field=None, **kw):
+    import torch
+    ny, nx = a11.shape
+    t11, t12 = torch.from_numpy(a11.copy()).to("cuda:0"), torch.from_numpy(a12.copy()).to("cuda:0")
+    f = None if v0_field is None else to_dev(v0_field)
+    ctx = fdm.fdm_transport_init(fdm.desc(nx, ny, v0_field=f, **kw), options={"precision": "fp64", "tile_rows": 7},
+                                 keep=[f])
+    dt = fdm.fdm_transport_dt(ctx)
+    fdm.fdm_transport_step(ctx, t11, t12, steps)
+    torch.cuda.synchronize()
+    fdm.fdm_destroy(ctx)
+    P = oracle_problem(oracle, nx, ny, dt, v0_field=v0_field, **kw)
+    o11, o12 = oracle.run(P, a11, a12, steps)
+    g11, g12 = t11.cpu().numpy(), t12.cpu().numpy()
+    assert np.isfinite(o11).all() and np.abs(o11).max() > 0
+    assert np.array_equal(g11, o11) and np.array_equal(g12, o12)
+
+
+def _state(nx=131, ny=45):
+    a11, a12 = W.ring(nx, ny, R=11.0, sigma=2.0)
+    b11, b12 = W.diagonal_bands(nx, ny, np.random.default_rng(3), n_bands=6)
+    return (a11 + 0.5 * b11).astype(np.float64), (a12 + 0.5 * b12).astype(np.float64)
+
+
+@pytest.mark.parametrize("exponent", [0, -149, -248, -250, -252, -300, -380, -500, -520, -540, 365, 371])
+@pytest.mark.parametrize("limiter", ["minmod", "superbee"])
+def test_scaled_densities(fdm, oracle, exponent, limiter):
+    a11, a12 = _state()
+    s = 2.0 ** exponent
+    _run(fdm, oracle, a11 * s, a12 * s, 4, limiter=limiter, v0=-1.0, cfl=0.4)
+
+
+@pytest.mark.parametrize("least", [-100, -249, -251, -400, -600, -1000])
+def test_mixed_scales_and_zeros(fdm, oracle, least):
+    a11, a12 = _state()
+    rng = np.random.default_rng(7)
+    for a in (a11, a12):
+        a *= 2.0 ** rng.integers(least, 1, size=a.shape)
+        a[rng.random(a.shape) < 0.3] = 0.0
+    v0 = (rng.uniform(-1, 1, a11.shape) * 2.0 ** rng.integers(-140, 1, size=a11.shape)).astype(np.float32)
+    v0[rng.random(v0.shape) < 0.2] = 0.0
+    v0[0, 0] = 1.0
+    _run(fdm, oracle, a11, a12, 2, v0_field=v0, limiter="mc", cfl=0.4)
+
+
+@pytest.mark.parametrize("dx,dy", [(0.25, 2.0), (0.3, 0.7), (1.0, 0.1), (3e-40, 2e-40)])
+@pytest.mark.parametrize("scheme,order,cfl", [("semidiscrete", 2, 0.3), ("fully_discrete", 1, 0.1)])
+def test_spacings(fdm, oracle, dx, dy, scheme, order, cfl):
+    a11, a12 = _state()
+    _run(fdm, oracle, a11, a12, 4, limiter="theta", theta=1.4, v0=-0.7, cfl=cfl, dx=dx, dy=dy, time_order=order,
+         scheme=scheme)
