@@ -142,7 +142,8 @@ typedef struct fdm_transport_desc {
 
 /* Scheduling options; pass NULL for the defaults. */
 typedef enum fdm_schedule {
-    FDM_SCHEDULE_AUTO = 0,     /* batched launches when n_instances > 1        */
+    FDM_SCHEDULE_AUTO = 0,     /* fused launches where they apply, else batched
+                                  ones when n_instances > 1, else plain        */
     FDM_SCHEDULE_BATCHED = 1,  /* one launch per stage for all instances       */
     FDM_SCHEDULE_PLAIN = 2,    /* one launch per stage per instance            */
     FDM_SCHEDULE_FUSED = 3     /* one launch per step (for all instances of a
@@ -186,9 +187,10 @@ typedef enum fdm_precision {
 
 typedef struct fdm_options {
     int32_t schedule;        /* fdm_schedule                                    */
-    int32_t tile_rows;       /* rows per wave tile; 0 picks a default (fused:
-                                at most five waves per SIMD where that gives
-                                4 to 64 rows); doubled until one instance's
+    int32_t tile_rows;       /* rows per wave tile; 0 picks a default (fused
+                                launches under AUTO: by a model of the launch
+                                time, 1 to 64 rows; FUSED: at most five waves
+                                per SIMD where that gives 4 to 64 rows); doubled until one instance's
                                 launch has at most 2^25 tiles (at the default
                                 heights only grids of at most three columns
                                 and over 2^29 rows need it); results do not

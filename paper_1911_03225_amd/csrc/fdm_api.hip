@@ -145,10 +145,6 @@ double static_mean_stress(const fdm_static_desc &d, const fdm::StaticParams &q)
     return 2.0 * d.mu * d.eps13 - d.mu * d.phi_mean * (double)q.h / (double)q.n3;
 }
 
-// Tiles (one wave64 each) of one launch: a dispatch holds fewer than 2^32
-// work-items, and the grid rounds the tile count up by at most 31.
-constexpr int64_t kMaxLaunchTiles = (int64_t)1 << 25;
-
 // Tallest balanced height the autotuner tries (one round of waves over a
 // 8192^2 grid needs 149 rows).
 constexpr int kMaxBalancedRows = 512;
@@ -170,17 +166,10 @@ int64_t launch_waves(const fdm_ctx *c, bool fused, bool batched, int rows)
 }
 
 // Smallest tile height whose launch has at most `limit` waves, or -1 if even
-// one tile per strip exceeds it.  launch_waves falls as the height grows.
+// one tile per strip exceeds it.
 int balanced_rows(const fdm_ctx *c, bool fused, bool batched, int max_ny, int64_t limit)
 {
-    if (launch_waves(c, fused, batched, max_ny) > limit) return -1;
-    int lo = 1, hi = max_ny;
-    while (lo < hi) {
-        const int mid = lo + (hi - lo) / 2;
-        if (launch_waves(c, fused, batched, mid) <= limit) hi = mid;
-        else lo = mid + 1;
-    }
-    return lo;
+    return balanced_height([&](int h) { return launch_waves(c, fused, batched, h); }, max_ny, limit);
 }
 
 void release(fdm_ctx *c)
@@ -240,17 +229,19 @@ fdm_status bind(fdm_ctx *c, void *const *a11, void *const *a12)
 // Enqueue n_steps on stream s for the bound arrays.
 fdm_status enqueue_steps(fdm_ctx *c, int32_t n_steps, hipStream_t s)
 {
-    if (c->fused) {   // both Heun stages per launch, ping-pong between the state and the stage buffer
-        for (int32_t step = 0; step < n_steps; ++step) {
-            if (c->batched)
-                FDM_HIP(c, fdm::launch_fused_batched(c->d_inst, c->d_tile_inst, c->total_tiles, step & 1,
-                                                     c->time_order == 3, s));
-            else
-                for (int i = 0; i < c->n; ++i)
-                    FDM_HIP(c, fdm::launch_fused(c->inst[i], step & 1, c->time_order == 3, s));
-        }
+    if (c->fused && !c->batched) {
+        for (int i = 0; i < c->n; ++i)
+            FDM_HIP(c, run_fused_steps(c->inst[i], c->desc[i], c->requested_rows, c->time_order, n_steps, s));
+        return FDM_OK;
     }
-    for (int32_t step = 0; step < (c->fused ? 0 : n_steps); ++step) {
+    if (c->fused) {   // both stages per launch, ping-pong between the state and the stage buffer
+        for (int32_t step = 0; step < n_steps; ++step)
+            FDM_HIP(c, fdm::launch_fused_batched(c->d_inst, c->d_tile_inst, c->total_tiles, step & 1,
+                                                 c->time_order == 3, s));
+        if (n_steps & 1) FDM_HIP(c, fdm::launch_copy_back_batched(c->d_inst, c->d_tile_inst, c->total_tiles, s));
+        return FDM_OK;
+    }
+    for (int32_t step = 0; step < n_steps; ++step) {
         int modes[2];
         const int nm = stage_modes(c->time_order, step, modes);
         for (int m = 0; m < nm; ++m) {
@@ -262,9 +253,9 @@ fdm_status enqueue_steps(fdm_ctx *c, int32_t n_steps, hipStream_t s)
             }
         }
     }
-    // Euler and the fused Heun step ping-pong between the state and the stage
-    // buffer; after an odd count the newest state sits in the stage buffer.
-    if ((c->time_order == 1 || c->fused) && (n_steps & 1)) {
+    // Euler ping-pongs between the state and the stage buffer; after an odd
+    // count the newest state sits in the stage buffer.
+    if (c->time_order == 1 && (n_steps & 1)) {
         for (int i = 0; i < c->n; ++i) {
             const int64_t n = (int64_t)c->inst[i].nx * c->inst[i].ny;
             FDM_HIP(c, fdm::launch_copy(c->inst[i].a11, c->inst[i].w11, n, c->precision, s));
@@ -285,13 +276,14 @@ fdm_status retile(fdm_ctx *c, int requested)
         batch_strip_rows += strip_rows_of(c->desc[i]);
         max_ny = std::max(max_ny, c->desc[i].ny);
     }
-    // The fused launch's default: the smallest height with at most five
-    // waves per SIMD, so every SIMD carries the same number of tiles (the
-    // autotuner's balanced heights; five per SIMD is within 1% of the best
-    // at 2048^2 and 4096^2).  The unfused rule where that height is below 4
-    // rows (small grids: the first stage's four extra rows would dominate)
-    // or above 64.
-    if (requested <= 0 && c->fused) {
+    // The default of the AUTO schedule's fused launch: fused_rows.  Where the
+    // fused schedule itself was asked for: the smallest height with at most
+    // five waves per SIMD, so every SIMD carries the same number of tiles
+    // (within 1% of the best at 2048^2 and 4096^2), or the unfused rule where
+    // that height is below 4 or above 64 rows.
+    if (requested <= 0 && c->fused && c->schedule == FDM_SCHEDULE_AUTO) {
+        requested = fused_rows([&](int h) { return launch_waves(c, true, c->batched, h); }, max_ny, c->simds);
+    } else if (requested <= 0 && c->fused) {
         const int r = balanced_rows(c, true, c->batched, max_ny, 5 * c->simds);
         if (r >= 4 && r <= 64) requested = r;
     }
@@ -305,9 +297,7 @@ fdm_status retile(fdm_ctx *c, int requested)
         // a launch of one instance must fit one dispatch: taller tiles where
         // the height asked for would exceed it (at the default heights only
         // grids of at most three columns and more than 2^29 rows)
-        const int64_t strips = c->fused ? I.fstrips : I.strips;
-        while (strips * fdm::tiles_along_y(d.ny, I.rows) > kMaxLaunchTiles && I.rows < d.ny)
-            I.rows = (int)std::min<int64_t>(d.ny, 2 * (int64_t)I.rows);
+        I.rows = launch_rows(c->fused ? I.fstrips : I.strips, d.ny, I.rows);
         I.chunks = fdm::tiles_along_y(d.ny, I.rows);
         I.tile_begin = tile;   // in the tiling of the schedule's kernel
         tile += (int64_t)(c->fused ? I.fstrips : I.strips) * I.chunks;
@@ -628,8 +618,7 @@ fdm_status fdm_transport_init(const fdm_transport_desc *descs, int32_t n_instanc
         order = o;
     }
     if (opt.schedule == FDM_SCHEDULE_FUSED &&
-        !(opt.precision == FDM_PRECISION_FP32 && (order == 2 || order == 3) &&
-          descs[0].scheme == FDM_SCHEME_SEMIDISCRETE))
+        !fused_applies(opt.precision, order, descs[0].scheme == FDM_SCHEME_FULLY_DISCRETE))
         return fail(nullptr, FDM_ERR_INVALID_ARG,
                     "the fused schedule needs FP32 precision, time_order 2 or 3 and the semi-discrete scheme");
     // Stability bound of the step: every case but a fixed dt over a celerity
@@ -649,7 +638,8 @@ fdm_status fdm_transport_init(const fdm_transport_desc *descs, int32_t n_instanc
     c->fd = descs[0].scheme == FDM_SCHEME_FULLY_DISCRETE;
     c->schedule = opt.schedule;
     c->precision = opt.precision;
-    c->fused = opt.schedule == FDM_SCHEDULE_FUSED;
+    c->fused = opt.schedule == FDM_SCHEDULE_FUSED ||
+               (opt.schedule == FDM_SCHEDULE_AUTO && fused_applies(opt.precision, order, c->fd));
     c->batched = n_instances > 1 && opt.schedule != FDM_SCHEDULE_PLAIN;   // fused: one launch for all
     c->desc.assign(descs, descs + n_instances);
     c->inst.resize(n_instances);
@@ -905,7 +895,7 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
     if (c->schedule == FDM_SCHEDULE_AUTO) {
         if (c->n > 1) schedules = {FDM_SCHEDULE_BATCHED, FDM_SCHEDULE_PLAIN};
         else schedules = {FDM_SCHEDULE_PLAIN};
-        if (c->precision == fdm::PREC_FP32 && (c->time_order == 2 || c->time_order == 3) && !c->fd)
+        if (fused_applies(c->precision, c->time_order, c->fd))
             schedules.push_back(FDM_SCHEDULE_FUSED);
     } else {
         schedules = {was_fused ? FDM_SCHEDULE_FUSED : was_batched ? FDM_SCHEDULE_BATCHED : FDM_SCHEDULE_PLAIN};
@@ -923,15 +913,17 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
         r = enqueue_steps(c, 1, c->stream);
         if (r != FDM_OK) return r;
         double best_t = 0.0;
+        // an odd fused count ends on the stage kernels: time an even one
+        const int32_t steps = trial_steps + (fused && trial_steps < INT32_MAX ? trial_steps & 1 : 0);
         for (int k = 0; k < reps; ++k) {
             FDM_HIP(c, hipEventRecord(e0, c->stream));
-            r = enqueue_steps(c, trial_steps, c->stream);
+            r = enqueue_steps(c, steps, c->stream);
             if (r != FDM_OK) return r;
             FDM_HIP(c, hipEventRecord(e1, c->stream));
             FDM_HIP(c, hipEventSynchronize(e1));
             float ms = 0.0f;
             FDM_HIP(c, hipEventElapsedTime(&ms, e0, e1));
-            const double t = 1e-3 * ms / trial_steps;
+            const double t = 1e-3 * ms / steps;
             if (k == 0 || t < best_t) best_t = t;
         }
         *out = best_t;

@@ -5,6 +5,7 @@
 
 #include <stdint.h>
 
+#include <functional>
 #include <string>
 
 #include "../../include/fdm.h"
@@ -46,12 +47,37 @@ void fill_inst(InstDev &I, const fdm_transport_desc &d, float dt, void *w11, voi
 // for `strip_rows` (strip, row) pairs in the launch.
 int pick_rows(int64_t strip_rows, int ny, int requested);
 
+// Whether a context may run the fused two-stage kernel: float32 state and
+// arithmetic, two stages a step, semi-discrete scheme.
+bool fused_applies(int32_t precision, int32_t order, bool fd);
+
+// Rows per tile of the fused kernel when neither a height nor the fused
+// schedule was asked for; waves(h) is the number of tiles at height h.
+int fused_rows(const std::function<int64_t(int)> &waves, int max_ny, int64_t simds);
+
+// Smallest tile height with at most `limit` tiles, or -1 if even one tile
+// per strip exceeds it (waves falls as the height grows).
+int balanced_height(const std::function<int64_t(int)> &waves, int max_ny, int64_t limit);
+
+// Tiles (one wave64 each) of one launch: a dispatch holds fewer than 2^32
+// work-items, and the grid rounds the tile count up by at most 31.
+constexpr int64_t kMaxLaunchTiles = (int64_t)1 << 25;
+
+// `rows`, doubled until a launch of one instance fits one dispatch.
+int launch_rows(int64_t strips, int ny, int rows);
+
 // (strip, row) pairs of one instance in the stage kernels' tiling.
 int64_t strip_rows_of(const fdm_transport_desc &d);
 
 // Stage launches of step number `step` for an integrator order (1 Euler,
 // 2 Heun, 3 explicit midpoint): the modes in order, their count returned.
 int stage_modes(int32_t order, int32_t step, int modes[2]);
+
+// n_steps of one instance by the fused kernel (order 2 or 3, float32), whose
+// launches go from the state to the stage buffer and back; the last of an odd
+// count by the stage kernels, in place.  rows: the tile height asked for, or 0.
+hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int32_t order, int32_t n_steps,
+                           hipStream_t s);
 
 // Message of the last failed call without a context (fdm_last_error(NULL)).
 void set_init_error(const std::string &msg);

@@ -123,6 +123,60 @@ int pick_rows(int64_t strip_rows, int ny, int requested)
     return (int)std::min<int64_t>(rows, ny);
 }
 
+bool fused_applies(int32_t precision, int32_t order, bool fd)
+{
+    return precision == FDM_PRECISION_FP32 && (order == 2 || order == 3) && !fd;
+}
+
+int balanced_height(const std::function<int64_t(int)> &waves, int max_ny, int64_t limit)
+{
+    if (waves(max_ny) > limit) return -1;
+    int lo = 1, hi = max_ny;
+    while (lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        if (waves(mid) <= limit) hi = mid;
+        else lo = mid + 1;
+    }
+    return lo;
+}
+
+// A launch that is resident at once takes the time of the SIMD with the most
+// waves, w, and a wave's time is linear in its height h.  Fitted over
+// 300 x 200 to 4096^2 and 1 to 75 rows (minmod, uniform celerity, us):
+//   3.4 + 0.75 w + (0.16 + 0.195 w) h,
+// the first part the launch, the loads and the first stage's extra rows, the
+// second the issue time of w waves (a lone wave also waits for its own
+// results, hence 0.16).  For each w the smallest h that fits it is the best;
+// at most seven waves are resident (66 to 72 registers).  Measured, this
+// choice against the best of all heights: 300 x 200 3.99 / 3.99 us a step,
+// 512^2 5.55 / 5.55, 1024^2 10.49 / 10.49, 1536^2 18.0 / 17.7, 2048^2
+// 26.1 / 26.1, 3000 x 1000 20.3 / 20.3, 4096^2 80.1 / 78.9; the stage
+// kernels' two launches take 7.09, 8.12, 13.7, -, 32.4, -, 165 at the sizes
+// where they were timed beside it.
+// Above 64 rows (beyond about 5000^2) the gain over 64 is under 2%.
+int fused_rows(const std::function<int64_t(int)> &waves, int max_ny, int64_t simds)
+{
+    int best = -1;
+    double least = 0.0;
+    for (int w = 1; w <= 7; ++w) {
+        const int h = balanced_height(waves, max_ny, w * simds);
+        if (h < 0 || h > 64) continue;
+        const double t = 3.4 + 0.75 * w + (0.16 + 0.195 * w) * h;
+        if (best < 0 || t < least) {
+            best = h;
+            least = t;
+        }
+    }
+    return best > 0 ? best : std::min(64, max_ny);
+}
+
+int launch_rows(int64_t strips, int ny, int rows)
+{
+    while (strips * tiles_along_y(ny, rows) > kMaxLaunchTiles && rows < ny)
+        rows = (int)std::min<int64_t>(ny, 2 * (int64_t)rows);
+    return rows;
+}
+
 int64_t strip_rows_of(const fdm_transport_desc &d)
 {
     return (int64_t)((d.nx + kStrip - 1) / kStrip) * d.ny;
@@ -193,6 +247,30 @@ int stage_modes(int32_t order, int32_t step, int modes[2])
     }
     modes[0] = (step & 1) ? MODE_BWD : MODE_FWD;
     return 1;
+}
+
+// The same bits either way.  The stage kernels' pair on the last odd step
+// costs no more than a fused launch and the copy of both components back
+// (2048^2: 32 us against 26 + 14; 512^2: 8.1 against 5.6 + 4).
+hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int32_t order, int32_t n_steps,
+                           hipStream_t s)
+{
+    for (int32_t step = 0; step + 1 < n_steps; step += 2)
+        for (int dir = 0; dir < 2; ++dir) {
+            const hipError_t e = launch_fused(I, dir, order == 3, s);
+            if (e != hipSuccess) return e;
+        }
+    if (!(n_steps & 1)) return hipSuccess;
+    InstDev J = I;
+    if (rows <= 0) J.rows = launch_rows(J.strips, d.ny, pick_rows(strip_rows_of(d), d.ny, 0));
+    J.chunks = tiles_along_y(d.ny, J.rows);
+    int modes[2];
+    const int nm = stage_modes(order, 0, modes);
+    for (int m = 0; m < nm; ++m) {
+        const hipError_t e = launch_stage(J, modes[m], PREC_FP32, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace host

@@ -231,6 +231,10 @@ hipError_t launch_fused(const InstDev &I, int dir, bool mid, hipStream_t s);
 // map and tile_begin of the fused tiling).
 hipError_t launch_fused_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles, int dir,
                                 bool mid, hipStream_t s);
+// After an odd number of batched fused steps: the stage buffers of every
+// instance back into the states, over the same tile map.
+hipError_t launch_copy_back_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles,
+                                    hipStream_t s);
 hipError_t launch_stats(const void *a11, const void *a12, int64_t n, int precision,
                         StatsPartial *d_partials, double *d_out, hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, int64_t n, int precision, hipStream_t s);

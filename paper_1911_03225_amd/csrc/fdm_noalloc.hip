@@ -30,10 +30,11 @@ __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void *g_scratch[kMaxDevices];   // device address of `scratch`, per device
+int64_t g_simds[kMaxDevices];   // SIMDs, per device
 
 // The current device's address of `scratch`, looked up on the first call on
 // that device (with the device current).
-hipError_t scratch_address(void **out)
+hipError_t scratch_address(void **out, int64_t *simds)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -45,9 +46,14 @@ hipError_t scratch_address(void **out)
         e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess) return e;
         if (!p) return hipErrorInvalidSymbol;
+        int cus = 0;
+        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess) return e;
+        g_simds[dev] = 4 * (int64_t)(cus > 1 ? cus : 1);
         g_scratch[dev] = p;
     }
     *out = g_scratch[dev];
+    *simds = g_simds[dev];
     return hipSuccess;
 }
 
@@ -91,7 +97,8 @@ extern "C" fdm_status fdm_transport_step_noalloc(const fdm_transport_desc *desc,
 
     hipStream_t s = (hipStream_t)hip_stream;
     void *base = nullptr;
-    hipError_t e = scratch_address(&base);
+    int64_t simds = 0;
+    hipError_t e = scratch_address(&base, &simds);
     if (e != hipSuccess) return device_error("hipGetSymbolAddress(scratch)", e);
     char *const stage = static_cast<char *>(base);
     float *const partials = reinterpret_cast<float *>(stage + kStageBytes);
@@ -117,8 +124,9 @@ extern "C" fdm_status fdm_transport_step_noalloc(const fdm_transport_desc *desc,
         smax = smax_uniform(d);
     }
 
-    // one instance, the default schedule of fdm_transport_init (one stage
-    // launch per stage, default tile height): the same kernels and bits
+    // one instance, the default schedule of fdm_transport_init (one fused
+    // launch per step where it applies, else one launch per stage; default
+    // tile height): the same kernels and bits
     InstDev I;
     fill_inst(I, d, step_dt(d, smax), stage, stage + (size_t)n * sizeof(float));
     I.a11 = alpha11;
@@ -127,6 +135,12 @@ extern "C" fdm_status fdm_transport_step_noalloc(const fdm_transport_desc *desc,
     I.strips = (d.nx + fdm::kStrip - 1) / fdm::kStrip;
     I.fstrips = (d.nx + fdm::kFusedStrip - 1) / fdm::kFusedStrip;
     I.chunks = fdm::tiles_along_y(d.ny, I.rows);
+    if (fused_applies(FDM_PRECISION_FP32, order, fd)) {
+        I.rows = fused_rows([&](int h) { return (int64_t)I.fstrips * fdm::tiles_along_y(d.ny, h); }, d.ny, simds);
+        I.chunks = fdm::tiles_along_y(d.ny, I.rows);
+        e = run_fused_steps(I, d, 0, order, n_steps, s);
+        return e == hipSuccess ? FDM_OK : device_error("fused launch", e);
+    }
     for (int32_t step = 0; step < n_steps; ++step) {
         int modes[2];
         const int nm = stage_modes(order, step, modes);

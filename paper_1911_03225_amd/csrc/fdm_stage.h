@@ -717,8 +717,8 @@ __device__ __forceinline__ void divide_spacings(double &dx, double &dy, const In
         dy *= I.rdyd;
         return;
     }
-    const bool ok = ((dx == 0.0) | (fabs(dx) >= 0x1p-900)) & ((dy == 0.0) | (fabs(dy) >= 0x1p-900));
-    if (I.spacing_kind == SPACING_SHARED && wave_all(ok)) {
+    const bool okx = dx == 0.0 || fabs(dx) >= 0x1p-900, oky = dy == 0.0 || fabs(dy) >= 0x1p-900;
+    if (I.spacing_kind == SPACING_SHARED && wave_all(okx && oky)) {
         dx = shared_quot(dx, I.dxd, I.rdxd);
         dy = shared_quot(dy, I.dyd, I.rdyd);
     } else {

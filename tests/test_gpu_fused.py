@@ -318,3 +318,36 @@ def test_coupled_run_on_a_fused_context(fdm):
         fdm.fdm_destroy(ctx)
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
     assert out[0][2] == out[1][2]
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 1), (64, 64), (57, 1), (300, 200), (513, 130), (1030, 520)])
+@pytest.mark.parametrize("order,steps", [(2, 1), (2, 2), (2, 5), (3, 4)])
+def test_auto_equals_plain_bitwise(fdm, nx, ny, order, steps):
+    """The AUTO schedule takes the fused launch (and the stage kernels for
+    the last step of an odd count): the plain schedule's bits."""
+    rng = np.random.default_rng(nx + ny)
+    a11, a12 = (rng.standard_normal((ny, nx)).astype(np.float32) for _ in range(2))
+    kw = dict(limiter="mc", cfl=0.4, v0=-0.8, time_order=order)
+    _, a = gpu_run(a11, a12, steps, **kw)
+    _, p = gpu_run(a11, a12, steps, options={"schedule": "plain"}, **kw)
+    assert np.array_equal(a[-1][1], p[-1][1]) and np.array_equal(a[-1][2], p[-1][2])
+
+
+@pytest.mark.parametrize("steps", [3, 4])
+def test_auto_batched_odd_steps_bitwise(fdm, steps):
+    """Several instances under AUTO: one fused launch a step, and after an
+    odd count one launch that copies every stage buffer back."""
+    import torch
+    rng = np.random.default_rng(5)
+    sizes = [(64, 64), (7, 3), (130, 55), (1, 40), (300, 90)]
+    cases = [tuple(rng.standard_normal((ny, nx)).astype(np.float32) for _ in range(2)) for nx, ny in sizes]
+    out = []
+    for sched in ("auto", "plain"):
+        t11, t12 = [to_dev(a) for a, _ in cases], [to_dev(b) for _, b in cases]
+        ctx = fdm.fdm_transport_init([fdm.desc(nx, ny, limiter="minmod", cfl=0.4, v0=1.0) for nx, ny in sizes],
+                                     options={"schedule": sched})
+        fdm.fdm_transport_step(ctx, t11, t12, steps)
+        torch.cuda.synchronize()
+        fdm.fdm_destroy(ctx)
+        out.append([t.cpu().numpy() for t in t11 + t12])
+    assert all(np.array_equal(x, y) for x, y in zip(*out))
