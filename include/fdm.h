@@ -142,8 +142,11 @@ typedef struct fdm_transport_desc {
 
 /* Scheduling options; pass NULL for the defaults. */
 typedef enum fdm_schedule {
-    FDM_SCHEDULE_AUTO = 0,     /* fused launches where they apply, else batched
-                                  ones when n_instances > 1, else plain        */
+    FDM_SCHEDULE_AUTO = 0,     /* one fused launch per step where it is faster
+                                  (FP32: wherever FUSED applies; one instance
+                                  in the FP64 modes: beyond the on-chip cache),
+                                  else batched launches when n_instances > 1,
+                                  else plain                                   */
     FDM_SCHEDULE_BATCHED = 1,  /* one launch per stage for all instances       */
     FDM_SCHEDULE_PLAIN = 2,    /* one launch per stage per instance            */
     FDM_SCHEDULE_FUSED = 3     /* one launch per step (for all instances of a

@@ -231,7 +231,8 @@ fdm_status enqueue_steps(fdm_ctx *c, int32_t n_steps, hipStream_t s)
 {
     if (c->fused && !c->batched) {
         for (int i = 0; i < c->n; ++i)
-            FDM_HIP(c, run_fused_steps(c->inst[i], c->desc[i], c->requested_rows, c->time_order, n_steps, s));
+            FDM_HIP(c, run_fused_steps(c->inst[i], c->desc[i], c->requested_rows, c->time_order, c->precision,
+                                       n_steps, s));
         return FDM_OK;
     }
     if (c->fused) {   // both stages per launch, ping-pong between the state and the stage buffer
@@ -639,7 +640,7 @@ fdm_status fdm_transport_init(const fdm_transport_desc *descs, int32_t n_instanc
     c->schedule = opt.schedule;
     c->precision = opt.precision;
     c->fused = opt.schedule == FDM_SCHEDULE_FUSED ||
-               (opt.schedule == FDM_SCHEDULE_AUTO && fused_applies(opt.precision, order, c->fd));
+               (opt.schedule == FDM_SCHEDULE_AUTO && fused_by_default(descs, n_instances, opt.precision, order));
     c->batched = n_instances > 1 && opt.schedule != FDM_SCHEDULE_PLAIN;   // fused: one launch for all
     c->desc.assign(descs, descs + n_instances);
     c->inst.resize(n_instances);

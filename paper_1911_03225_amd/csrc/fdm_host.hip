@@ -128,6 +128,24 @@ bool fused_applies(int32_t precision, int32_t order, bool fd)
     return precision == FDM_PRECISION_FP32 && (order == 2 || order == 3) && !fd;
 }
 
+// In float32 the fused kernel is faster at every size.  In the FP64 modes it
+// issues 1.2 times the stage kernels' arithmetic (halo lanes and rows) at
+// half their waves per SIMD, so it pays only where the two launches are bound
+// by memory, that is where state, stage buffer and field exceed the 256 MB
+// on-chip cache: 4096^2 with a field 330 us a step against 360 to 393
+// (float32 state 297 against 316), but 1536^2 69 against 61.  One instance
+// only: the batched FP64 launches have no fused form.
+bool fused_by_default(const fdm_transport_desc *descs, int32_t n, int32_t precision, int32_t order)
+{
+    const fdm_transport_desc &d = descs[0];
+    const bool fd = d.scheme == FDM_SCHEME_FULLY_DISCRETE;
+    if (precision == FDM_PRECISION_FP32) return fused_applies(precision, order, fd);
+    if (n > 1 || !fused_applies(FDM_PRECISION_FP32, order, fd)) return false;
+    const bool field = d.velocity == FDM_VELOCITY_LAW && d.v0_field;
+    const int64_t per_node = (precision == FDM_PRECISION_FP64 ? 32 : 16) + (field ? 4 : 0);
+    return (int64_t)d.nx * d.ny * per_node > (int64_t)256 << 20;
+}
+
 int balanced_height(const std::function<int64_t(int)> &waves, int max_ny, int64_t limit)
 {
     if (waves(max_ny) > limit) return -1;
@@ -252,12 +270,12 @@ int stage_modes(int32_t order, int32_t step, int modes[2])
 // The same bits either way.  The stage kernels' pair on the last odd step
 // costs no more than a fused launch and the copy of both components back
 // (2048^2: 32 us against 26 + 14; 512^2: 8.1 against 5.6 + 4).
-hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int32_t order, int32_t n_steps,
-                           hipStream_t s)
+hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int32_t order, int32_t precision,
+                           int32_t n_steps, hipStream_t s)
 {
     for (int32_t step = 0; step + 1 < n_steps; step += 2)
         for (int dir = 0; dir < 2; ++dir) {
-            const hipError_t e = launch_fused(I, dir, order == 3, s);
+            const hipError_t e = launch_fused(I, dir, order == 3, precision, s);
             if (e != hipSuccess) return e;
         }
     if (!(n_steps & 1)) return hipSuccess;
@@ -267,7 +285,7 @@ hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int ro
     int modes[2];
     const int nm = stage_modes(order, 0, modes);
     for (int m = 0; m < nm; ++m) {
-        const hipError_t e = launch_stage(J, modes[m], PREC_FP32, s);
+        const hipError_t e = launch_stage(J, modes[m], precision, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

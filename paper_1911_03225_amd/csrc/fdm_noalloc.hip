@@ -138,7 +138,7 @@ extern "C" fdm_status fdm_transport_step_noalloc(const fdm_transport_desc *desc,
     if (fused_applies(FDM_PRECISION_FP32, order, fd)) {
         I.rows = fused_rows([&](int h) { return (int64_t)I.fstrips * fdm::tiles_along_y(d.ny, h); }, d.ny, simds);
         I.chunks = fdm::tiles_along_y(d.ny, I.rows);
-        e = run_fused_steps(I, d, 0, order, n_steps, s);
+        e = run_fused_steps(I, d, 0, order, FDM_PRECISION_FP32, n_steps, s);
         return e == hipSuccess ? FDM_OK : device_error("fused launch", e);
     }
     for (int32_t step = 0; step < n_steps; ++step) {

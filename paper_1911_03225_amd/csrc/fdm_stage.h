@@ -933,7 +933,12 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
         if constexpr (HSUM) hacc += (out_col && it < nrows) ? hv : R(0);
 
         R dhx = hr - hv, dhy = hv - hprev;
-        if constexpr (kF64) divide_spacings(dhx, dhy, I);
+        if constexpr (kF64 && kFD) {
+            dhx /= I.dxd;
+            dhy /= I.dyd;
+        } else if constexpr (kF64) {
+            divide_spacings(dhx, dhy, I);
+        }
         {   // x-edge (j+1/2, k): d(alpha_12)/dt = -(Hhat_{j+1} - Hhat_j)/dx; not on the extra row
             R nv;
             const R from = MODE == MODE_MID2 ? b12 : wx;   // the state the stage adds to
@@ -986,7 +991,7 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
 
 // ------------------------------------------------------------ fused Heun
 //
-// Both Heun stages in one pass (float only, semi-discrete scheme): each wave
+// Both Heun stages in one pass (semi-discrete scheme): each wave
 // runs the first stage three node rows ahead of the second and keeps the
 // first stage's densities in registers, so a step reads the state (and the
 // celerity field) once and writes the new state once -- 8 B per node in and
@@ -997,28 +1002,35 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
 // same operations as in the unfused kernels (same node function, same
 // updates), so the result is the same bit for bit.  Reads src, writes dst
 // (distinct buffers: neighbouring tiles still read src).
+//
+// float: the two stages' nodes of an iteration in lock step (F2).  FP64: one
+// after the other, each with its own fall-back to the definition's form; in
+// lock step the registers of both (200) left two waves per SIMD and 4096^2
+// took 339 us a step against 330 (and the unit 2.5 minutes to compile).
 constexpr int kFStrip = kFusedStrip, kFHalo = 4;
 // The fused kernel's loads run kFAhead rows ahead of stage A (at most five:
 // A's alpha_11 ring holds rows m-1 .. m+kFAhead+1 in eight slots).
 constexpr int kFAhead = 2;
 static_assert(kFAhead >= 1 && kFAhead <= 5, "fused look-ahead must fit the eight-slot rings");
 
-template <int LK, int VK, bool FIELD, bool MID = false>
+template <typename R, typename S, int LK, int VK, bool FIELD, bool MID>
 __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int chunk, int lane, const void *src11,
                                                const void *src12, void *dst11, void *dst12)
 {
-    using R = float;
-    using S = float;
+    constexpr bool kF64 = sizeof(R) == 8;
+    constexpr bool kShared = kF64 && VK == VK_LAW;   // the shared-reciprocal evaluation applies
     const int nx = I.nx, ny = I.ny;
-    const R theta = I.theta, cx = I.cx, cy = I.cy;
+    const R theta = kF64 ? R(I.thetad) : R(I.theta);
+    // float: dt/dx, dt/dy; FP64: the step itself, the spacings divide
+    const R cx = kF64 ? R(I.dtd) : R(I.cx), cy = kF64 ? R(I.dtd) : R(I.cy);
     // explicit midpoint: stage A advances half a step (halving is exact)
-    const R cxa = MID ? 0.5f * cx : cx, cya = MID ? 0.5f * cy : cy;
-    const R V1 = I.V1, V2 = I.V2;
+    const R cxa = MID ? R(0.5) * cx : cx, cya = MID ? R(0.5) * cy : cy;
+    const R V1 = R(I.V1), V2 = R(I.V2);
 
     const int gcol = strip * kFStrip - kFHalo + lane;
     int col = gcol % nx;
     if (col < 0) col += nx;
-    const uint32_t off = (uint32_t)col * 4u;
+    const uint32_t off = (uint32_t)col * (uint32_t)sizeof(S), off_v = (uint32_t)col * 4u;
     const bool out_col = lane >= kFHalo && lane < kFHalo + kFStrip && gcol < nx;
     const int k0 = chunk * I.rows;
     const int nrows = min(I.rows, ny - k0);
@@ -1054,9 +1066,19 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
     y[0] = at(row_ptr<S>(src11, kf, nx), off);
     slA[1] = limited_slope<LK>(ym2, R(y[7]), R(y[0]), theta);
     hhA[1] = R(0);
+    // float: the carried y differences and their scaled forms (B's are set
+    // after the first five iterations); FP64: which of the last rows of
+    // alpha_11 (A's input, A's output) hold values out of the shared
+    // evaluation's range
     float ydmA = float(R(y[0]) - R(y[7]));
     float ydmsA = LK == LK_SUPERBEE ? 2.0f * ydmA : float(theta) * ydmA;
-    float ydmB = 0.0f, ydmsB = 0.0f;   // set after the first five iterations
+    float ydmB = 0.0f, ydmsB = 0.0f;
+    int outA = 0, outB = 0;
+    if constexpr (kShared) {
+        if (!wave_all(edge_in_range(S(ym2)))) outA |= 4;
+        if (!wave_all(edge_in_range(y[7]))) outA |= 2;
+        if (!wave_all(edge_in_range(y[0]))) outA |= 1;
+    }
 
     const int lastA = nrows + 4;   // A's last row that B needs
     const int last = nrows + 5;    // B's last iteration
@@ -1065,7 +1087,7 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         const int kf1 = next_row(kf, ny);
         wx_[j] = at(row_ptr<S>(src12, kf, nx), off);
         y[j + 1] = at(row_ptr<S>(src11, kf1, nx), off);
-        if constexpr (FIELD) v0_[j] = at(row_ptr<float>(I.v0f, kf, nx), off);
+        if constexpr (FIELD) v0_[j] = at(row_ptr<float>(I.v0f, kf, nx), off_v);
         kf = kf1;
     }
     int kf1 = next_row(kf, ny);
@@ -1088,15 +1110,41 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         return numerical_hamiltonian<VK>(pxm, pxp, pym, pyp, v0, T(V1), T(V2));
     };
 
+    // FP64: the slope and the four face values (x -, x +, y -, y +) of a node.
+    auto faces64 = [&](R ym1, R y0, R yp1, R wx, R slhp, R &s0, R (&p)[4]) {
+        s0 = limited_slope<LK>(ym1, y0, yp1, theta);
+        p[3] = -madd(R(-0.5), s0, y0);
+        p[2] = -madd(R(0.5), slhp, ym1);
+        const R wl = from_left(wx), wr = from_right(wx);
+        const R sx = limited_slope<LK>(wl, wx, wr, theta);
+        p[1] = madd(R(-0.5), sx, wx);
+        p[0] = from_left(madd(R(0.5), sx, wx));
+    };
+
+    // The rows of a sliding window that hold values out of range: one more row.
+    auto out_of_range = [&](int out, S next) { return (out << 1 | (wave_all(edge_in_range(next)) ? 0 : 1)) & 15; };
+    // The numerical Hamiltonian from the face values, shared where it applies.
+    auto hamiltonian64 = [&](const R (&q)[4], R v0, int out, S wx) -> R {
+        R hv;
+        bool fine = false;
+        if constexpr (kShared) {
+            const bool ok = numerical_hamiltonian_shared(q[0], q[1], q[2], q[3], v0, hv);
+            fine = out == 0 && wave_all(ok & edge_in_range(wx));
+        }
+        if (!fine) hv = numerical_hamiltonian_ieee<VK>(q[0], q[1], q[2], q[3], v0, V1, V2);
+        return hv;
+    };
+
     // A's outputs at ring phase p from its Hhat at row m and at the node to
     // the right: alpha_12 of row m and alpha_11 of row m-1 after stage 1.
     auto update_a = [&](auto phase, R hv, R hr, R wx, R ym1) {
         constexpr int p = decltype(phase)::value;
         constexpr int h = p & 1, hp = h ^ 1;
-        const R hprev = hhA[hp];
+        R dx = hr - hv, dy = hv - hhA[hp];
+        if constexpr (kF64) divide_spacings(dx, dy, I);
         hhA[h] = hv;
-        wxo[p & 3] = S(madd(-cxa, hr - hv, wx));
-        wyo[(p + 3) & 3] = S(madd(cya, hv - hprev, ym1));
+        wxo[p & 3] = S(kF64 ? wx + cxa * -dx : madd(-cxa, dx, wx));
+        wyo[(p + 3) & 3] = S(madd(cya, dy, ym1));
     };
     // B's outputs: alpha_12 of row kB and alpha_11 of the row above.  Heun:
     // the mean of the state and one more stage; midpoint: the state plus a
@@ -1105,15 +1153,16 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         constexpr int p = decltype(phase)::value;
         constexpr int h = p & 1, hp = h ^ 1;
         const int bi = it - 5;
-        const R hprev = hhB[hp];
+        R dx = hr - hv, dy = hv - hhB[hp];
+        if constexpr (kF64) divide_spacings(dx, dy, I);
         hhB[h] = hv;
         {
-            R nv = madd(-cx, hr - hv, MID ? b12 : wx);
+            R nv = kF64 ? (MID ? b12 : wx) + cx * -dx : madd(-cx, dx, MID ? b12 : wx);
             if constexpr (!MID) nv = madd(R(0.5), b12, R(0.5) * nv);
             put(row_ptr<S>(dst12, kB, nx, bi < nrows), off_st, S(nv));
         }
         {
-            R nv = madd(cy, hv - hprev, MID ? b11 : ym1);
+            R nv = madd(cy, dy, MID ? b11 : ym1);
             if constexpr (!MID) nv = madd(R(0.5), b11, R(0.5) * nv);
             put(row_ptr<S>(dst11, kBprev, nx, bi > 0), off_st, S(nv));
         }
@@ -1136,7 +1185,7 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         const bool live = it + kFAhead <= lastA;
         wx_[(p + kFAhead) & 7] = at(row_ptr<S>(src12, kf, nx, live), off);
         y[(p + kFAhead + 1) & 7] = at(row_ptr<S>(src11, kf1, nx, live), off);
-        if constexpr (FIELD) v0_[(p + kFAhead) & 7] = at(row_ptr<float>(I.v0f, kf, nx, live), off);
+        if constexpr (FIELD) v0_[(p + kFAhead) & 7] = at(row_ptr<float>(I.v0f, kf, nx, live), off_v);
         kf = kf1;
         kf1 = next_row(kf1, ny);
     };
@@ -1147,7 +1196,15 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         constexpr int h = p & 1, hp = h ^ 1;
         R ym1, y0, yp1, wx, v0;
         operands_a(it, phase, ym1, y0, yp1, wx, v0);
-        const R hv = node(ym1, y0, yp1, wx, v0, slA[hp], slA[h], ydmA, ydmsA);
+        R hv;
+        if constexpr (kF64) {
+            R q[4];
+            faces64(ym1, y0, yp1, wx, slA[hp], slA[h], q);
+            if constexpr (kShared) outA = out_of_range(outA, y[(p + 1) & 7]);
+            hv = hamiltonian64(q, v0, outA, S(wx));
+        } else {
+            hv = node(ym1, y0, yp1, wx, v0, slA[hp], slA[h], ydmA, ydmsA);
+        }
         update_a(phase, hv, from_right(hv), wx, ym1);
     };
 
@@ -1165,6 +1222,11 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         ydmB = float(c - b);
         ydmsB = LK == LK_SUPERBEE ? 2.0f * ydmB : float(theta) * ydmB;
         hhB[0] = R(0);
+        if constexpr (kShared) {
+            if (!wave_all(edge_in_range(wyo[0]))) outB |= 4;
+            if (!wave_all(edge_in_range(wyo[1]))) outB |= 2;
+            if (!wave_all(edge_in_range(wyo[2]))) outB |= 1;
+        }
     }
     // Iterations from 5 on: A at row m and B at row kB = m - 3, their node
     // evaluations in lock step (independent: B reads what A wrote on
@@ -1178,6 +1240,18 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         const R wxb = R(wxo[(p + 1) & 3]);
         const R v0b = FIELD ? R(vb_[(p + 1) & 3]) : R(I.v0);
         const R b12 = R(b12_[(p + 1) & 3]), b11 = R(b11_[p & 3]);   // the step's initial state
+        if constexpr (kF64) {
+            R q[4], hv;
+            faces64(ym1a, y0a, yp1a, wxa, slA[hp], slA[h], q);
+            if constexpr (kShared) outA = out_of_range(outA, y[(p + 1) & 7]);
+            hv = hamiltonian64(q, v0a, outA, S(wxa));
+            update_a(phase, hv, from_right(hv), wxa, ym1a);
+            faces64(ym1b, y0b, yp1b, wxb, slB[hp], slB[h], q);
+            if constexpr (kShared) outB = out_of_range(outB, wyo[(p + 2) & 3]);
+            hv = hamiltonian64(q, v0b, outB, S(wxb));
+            update_b(phase, it, hv, from_right(hv), wxb, ym1b, b12, b11);
+            return;
+        } else {
         F2 s0, ydm(ydmA, ydmB), ydms(ydmsA, ydmsB);
         const F2 hv = node(F2(ym1a, ym1b), F2(y0a, y0b), F2(yp1a, yp1b), F2(wxa, wxb), F2(v0a, v0b),
                            F2(slA[hp], slB[hp]), s0, ydm, ydms);
@@ -1190,6 +1264,7 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         const F2 hr = from_right(hv);
         update_a(phase, hv.a, hr.a, wxa, ym1a);
         update_b(phase, it, hv.b, hr.b, wxb, ym1b, b12, b11);
+        }
     };
     for (int it = 5;; it += 8) {
         body(it, Phase<5>{});
@@ -1297,7 +1372,7 @@ hipError_t launch_stage_t(const InstDev &I, int mode, hipStream_t s)
 
 // Fused Heun step: dir 0 reads the state and writes the stage buffer, dir 1
 // the other way round.
-template <int LK, int VK, bool FIELD, bool MID>
+template <typename R, typename S, int LK, int VK, bool FIELD, bool MID>
 __global__ __launch_bounds__(kBlock) void fused_kernel(InstDev I, int64_t total_tiles, int blocks_per_xcd,
                                                        int strips, int dir)
 {
@@ -1306,7 +1381,7 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(InstDev I, int64_t total_
     const int t = (int)tile;
     const void *s11 = dir ? I.w11 : I.a11, *s12 = dir ? I.w12 : I.a12;
     void *d11 = dir ? I.a11 : I.w11, *d12 = dir ? I.a12 : I.w12;
-    run_tile_fused<LK, VK, FIELD, MID>(I, t % strips, t / strips, threadIdx.x & 63, s11, s12, d11, d12);
+    run_tile_fused<R, S, LK, VK, FIELD, MID>(I, t % strips, t / strips, threadIdx.x & 63, s11, s12, d11, d12);
 }
 
 // Batched fused step: one launch for the fused tiles of every instance;
@@ -1326,22 +1401,34 @@ __global__ __launch_bounds__(kBlock) void fused_kernel_batched(const InstDev *__
     void *d11 = DIR ? I.a11 : I.w11, *d12 = DIR ? I.a12 : I.w12;
     with_limiter<true>(I.limiter, [&](auto t) {
         constexpr int L = decltype(t)::value;
-        if (I.vkind == VK_PRESCRIBED) run_tile_fused<L, VK_PRESCRIBED, false, MID>(I, strip, chunk, lane, s11, s12, d11, d12);
-        else if (I.v0f != nullptr) run_tile_fused<L, VK_LAW, true, MID>(I, strip, chunk, lane, s11, s12, d11, d12);
-        else run_tile_fused<L, VK_LAW, false, MID>(I, strip, chunk, lane, s11, s12, d11, d12);
+        if (I.vkind == VK_PRESCRIBED) run_tile_fused<float, float, L, VK_PRESCRIBED, false, MID>(I, strip, chunk, lane, s11, s12, d11, d12);
+        else if (I.v0f != nullptr) run_tile_fused<float, float, L, VK_LAW, true, MID>(I, strip, chunk, lane, s11, s12, d11, d12);
+        else run_tile_fused<float, float, L, VK_LAW, false, MID>(I, strip, chunk, lane, s11, s12, d11, d12);
     });
 }
 
-template <int LK, int VK, bool FIELD, bool MID>
+template <typename R, typename S, int LK, int VK, bool FIELD, bool MID>
 hipError_t launch_fused_t(const InstDev &I, int dir, hipStream_t s)
 {
     const int strips = (I.nx + kFStrip - 1) / kFStrip;
     const int64_t tiles = (int64_t)strips * tiles_along_y(I.ny, I.rows);
     const int64_t blocks = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     const int per_xcd = (int)((blocks + 7) / 8);
-    hipLaunchKernelGGL((fused_kernel<LK, VK, FIELD, MID>), dim3(8 * per_xcd), dim3(kBlock), 0, s, I, tiles, per_xcd,
+    hipLaunchKernelGGL((fused_kernel<R, S, LK, VK, FIELD, MID>), dim3(8 * per_xcd), dim3(kBlock), 0, s, I, tiles, per_xcd,
                        strips, dir);
     return hipGetLastError();
+}
+
+template <typename R, typename S, bool MID>
+hipError_t launch_fused_r(const InstDev &I, int dir, hipStream_t s)
+{
+    if (I.vkind != VK_LAW && I.vkind != VK_PRESCRIBED) return hipErrorInvalidValue;   // semi-discrete scheme only
+    return with_limiter<sizeof(R) == 4>(I.limiter, [&](auto t) -> hipError_t {
+        constexpr int L = decltype(t)::value;
+        if (I.vkind == VK_PRESCRIBED) return launch_fused_t<R, S, L, VK_PRESCRIBED, false, MID>(I, dir, s);
+        if (I.v0f != nullptr) return launch_fused_t<R, S, L, VK_LAW, true, MID>(I, dir, s);
+        return launch_fused_t<R, S, L, VK_LAW, false, MID>(I, dir, s);
+    });
 }
 
 // Dispatch of one instance's stage launch over limiter, Hamiltonian and

@@ -15,23 +15,9 @@ hipError_t launch_stage_f32(const InstDev &I, int mode, hipStream_t s)
     return launch_stage_r<float, float>(I, mode, s);
 }
 
-namespace {
-template <bool MID>
-hipError_t launch_fused_r(const InstDev &I, int dir, hipStream_t s)
+hipError_t launch_fused_f32(const InstDev &I, int dir, bool mid, hipStream_t s)
 {
-    if (I.vkind != VK_LAW && I.vkind != VK_PRESCRIBED) return hipErrorInvalidValue;   // semi-discrete scheme only
-    return with_limiter<true>(I.limiter, [&](auto t) -> hipError_t {
-        constexpr int L = decltype(t)::value;
-        if (I.vkind == VK_PRESCRIBED) return launch_fused_t<L, VK_PRESCRIBED, false, MID>(I, dir, s);
-        if (I.v0f != nullptr) return launch_fused_t<L, VK_LAW, true, MID>(I, dir, s);
-        return launch_fused_t<L, VK_LAW, false, MID>(I, dir, s);
-    });
-}
-}  // namespace
-
-hipError_t launch_fused(const InstDev &I, int dir, bool mid, hipStream_t s)
-{
-    return mid ? launch_fused_r<true>(I, dir, s) : launch_fused_r<false>(I, dir, s);
+    return mid ? launch_fused_r<float, float, true>(I, dir, s) : launch_fused_r<float, float, false>(I, dir, s);
 }
 
 hipError_t launch_fused_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles, int dir,

@@ -74,3 +74,36 @@ def test_spacings(fdm, oracle, dx, dy, scheme, order, cfl):
     a11, a12 = _state()
     _run(fdm, oracle, a11, a12, 4, limiter="theta", theta=1.4, v0=-0.7, cfl=cfl, dx=dx, dy=dy, time_order=order,
          scheme=scheme)
+
+
+@pytest.mark.parametrize("precision,order", [("fp64", 2), ("fp64_arith", 3)])
+def test_fused_beyond_the_on_chip_cache(fdm, precision, order):
+    """One grid whose state, stage buffer and field exceed 256 MB takes the
+    fused kernel under AUTO: the plain schedule's bits (the stage kernels are
+    pinned to the oracle), for an even and an odd number of steps, with values
+    that leave the shared evaluation's range in some rows."""
+    import torch
+    nx, ny = (3001, 2911) if precision == "fp64" else (4001, 3911)
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    rng = np.random.default_rng(11)
+    g = torch.Generator(device="cuda:0").manual_seed(4)
+    field = (torch.rand(ny, nx, generator=g, device="cuda:0") - 0.5).contiguous()
+    state = []
+    for k in range(2):
+        a = torch.randn(ny, nx, generator=g, device="cuda:0", dtype=dt)
+        a[:, 100:900] = 0.0
+        r = int(rng.integers(0, ny - 60))
+        a[r:r + 40] *= 1e-30 if precision == "fp64_arith" else 1e-120
+        state.append(a)
+    out = []
+    for sched in ("auto", "plain"):
+        t11, t12 = state[0].clone(), state[1].clone()
+        ctx = fdm.fdm_transport_init(fdm.desc(nx, ny, limiter="mc", cfl=0.4, v0_field=field, time_order=order),
+                                     options={"precision": precision, "schedule": sched}, keep=[field])
+        fdm.fdm_transport_step(ctx, t11, t12, 2)
+        fdm.fdm_transport_step(ctx, t11, t12, 1)
+        torch.cuda.synchronize()
+        fdm.fdm_destroy(ctx)
+        out.append((t11, t12))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    assert torch.isfinite(out[0][0]).all()
