@@ -231,8 +231,8 @@ fdm_status enqueue_steps(fdm_ctx *c, int32_t n_steps, hipStream_t s)
 {
     if (c->fused && !c->batched) {
         for (int i = 0; i < c->n; ++i)
-            FDM_HIP(c, run_fused_steps(c->inst[i], c->desc[i], c->requested_rows, c->time_order, c->precision,
-                                       n_steps, s));
+            FDM_HIP(c, run_fused_steps(c->inst[i], c->desc[i], c->requested_rows, c->simds, c->time_order,
+                                       c->precision, n_steps, s));
         return FDM_OK;
     }
     if (c->fused) {   // both stages per launch, ping-pong between the state and the stage buffer
@@ -288,11 +288,15 @@ fdm_status retile(fdm_ctx *c, int requested)
         const int r = balanced_rows(c, true, c->batched, max_ny, 5 * c->simds);
         if (r >= 4 && r <= 64) requested = r;
     }
+    // The stage kernels' default.
+    if (requested <= 0 && !c->fused && c->batched)
+        requested = stage_rows([&](int h) { return launch_waves(c, false, true, h); }, batch_strip_rows, max_ny, c->simds);
     int64_t tile = 0;
     for (int i = 0; i < c->n; ++i) {
         const fdm_transport_desc &d = c->desc[i];
         InstDev &I = c->inst[i];
-        I.rows = pick_rows(c->batched ? batch_strip_rows : strip_rows_of(d), d.ny, requested);
+        if (requested <= 0 && !c->fused) I.rows = stage_rows_of(d, c->simds);
+        else I.rows = pick_rows(c->batched ? batch_strip_rows : strip_rows_of(d), d.ny, requested);
         I.strips = (d.nx + fdm::kStrip - 1) / fdm::kStrip;
         I.fstrips = (d.nx + fdm::kFusedStrip - 1) / fdm::kFusedStrip;
         // a launch of one instance must fit one dispatch: taller tiles where
@@ -440,7 +444,7 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
     if (c->fused && c->requested_rows <= 0) {
         // the stage kernels' default tiling, as on a plain context: the per-tile
         // sums then add in the same order whatever the schedule
-        I.rows = pick_rows(strip_rows_of(d), d.ny, 0);
+        I.rows = launch_rows(I.strips, d.ny, stage_rows_of(d, c->simds));
         I.chunks = fdm::tiles_along_y(d.ny, I.rows);
     }
     const int64_t tiles = (int64_t)I.strips * I.chunks;

@@ -43,8 +43,8 @@ int spacing_kind(double dx, double dy);
 // the state pointers and the tiling are left unset.
 void fill_inst(InstDev &I, const fdm_transport_desc &d, float dt, void *w11, void *w12);
 
-// Rows per wave tile of the stage kernels: `requested`, or the default rule
-// for `strip_rows` (strip, row) pairs in the launch.
+// Rows per wave tile of large launches: `requested`, or by the number of
+// `strip_rows` (strip, row) pairs in the launch.
 int pick_rows(int64_t strip_rows, int ny, int requested);
 
 // Whether the fused schedule may be asked for: float32 state and arithmetic,
@@ -53,6 +53,13 @@ bool fused_applies(int32_t precision, int32_t order, bool fd);
 
 // Whether the AUTO schedule takes the fused kernel.
 bool fused_by_default(const fdm_transport_desc *descs, int32_t n, int32_t precision, int32_t order);
+
+// Rows per tile of the stage kernels when no height was asked for; waves(h)
+// is the number of tiles at height h, strip_rows the (strip, row) pairs.
+int stage_rows(const std::function<int64_t(int)> &waves, int64_t strip_rows, int max_ny, int64_t simds);
+
+// stage_rows for one instance.
+int stage_rows_of(const fdm_transport_desc &d, int64_t simds);
 
 // Rows per tile of the fused kernel when neither a height nor the fused
 // schedule was asked for; waves(h) is the number of tiles at height h.
@@ -79,8 +86,8 @@ int stage_modes(int32_t order, int32_t step, int modes[2]);
 // n_steps of one instance by the fused kernel (order 2 or 3, float32), whose
 // launches go from the state to the stage buffer and back; the last of an odd
 // count by the stage kernels, in place.  rows: the tile height asked for, or 0.
-hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int32_t order, int32_t precision,
-                           int32_t n_steps, hipStream_t s);
+hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds, int32_t order,
+                           int32_t precision, int32_t n_steps, hipStream_t s);
 
 // Message of the last failed call without a context (fdm_last_error(NULL)).
 void set_init_error(const std::string &msg);

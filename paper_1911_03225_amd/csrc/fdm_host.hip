@@ -158,6 +158,43 @@ int balanced_height(const std::function<int64_t(int)> &waves, int max_ny, int64_
     return lo;
 }
 
+// As in fused_rows below: the SIMD with the most waves, w, sets the time of a
+// launch that is resident at once, an iteration of a wave's row loop takes
+// about as long again with each wave more (a lone wave also waits for its own
+// results), and a tile of h rows costs h + 3 of them with its extra row and
+// its first loads.  So the height is the smallest that fits w waves per SIMD
+// for the w of 1 .. 8 with the least (h + 3)(1 + w).  Measured against
+// pick_rows (us a step): fully discrete 64^2 2.77 / 3.64, 300 x 200 2.81 /
+// 3.73, 512^2 4.28 / 4.49, 1009 x 757 6.29 / 6.86, 1536^2 12.2 / 13.0;
+// float64 state, both stages, 64^2 7.5 / 11.5, 512^2 14.1 / 16.9, 1009 x 757
+// 24.9 / 29.4, 1536^2 58.2 / 60.9.  Launches of more than 5 waves per SIMD at
+// pick_rows' height keep it, the evenness matters less there: 2048^2 fully
+// discrete 17.5 at its 12 rows against 17.7 at the balanced 18, 4096^2 61.0 at
+// 16 against 62.6 at 36.
+int stage_rows(const std::function<int64_t(int)> &waves, int64_t strip_rows, int max_ny, int64_t simds)
+{
+    const int large = pick_rows(strip_rows, max_ny, 0);
+    if (waves(large) > 5 * simds) return large;
+    int best = -1;
+    int64_t least = 0;
+    for (int w = 1; w <= 8; ++w) {
+        const int h = balanced_height(waves, max_ny, w * simds);
+        if (h < 0) continue;
+        const int64_t t = ((int64_t)h + 3) * (1 + w);
+        if (best < 0 || t < least) {
+            best = h;
+            least = t;
+        }
+    }
+    return best > 0 ? best : large;
+}
+
+int stage_rows_of(const fdm_transport_desc &d, int64_t simds)
+{
+    const int64_t strips = (d.nx + kStrip - 1) / kStrip;
+    return stage_rows([&](int h) { return strips * tiles_along_y(d.ny, h); }, strip_rows_of(d), d.ny, simds);
+}
+
 // A launch that is resident at once takes the time of the SIMD with the most
 // waves, w, and a wave's time is linear in its height h.  Fitted over
 // 300 x 200 to 4096^2 and 1 to 75 rows (minmod, uniform celerity, us):
@@ -270,8 +307,8 @@ int stage_modes(int32_t order, int32_t step, int modes[2])
 // The same bits either way.  The stage kernels' pair on the last odd step
 // costs no more than a fused launch and the copy of both components back
 // (2048^2: 32 us against 26 + 14; 512^2: 8.1 against 5.6 + 4).
-hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int32_t order, int32_t precision,
-                           int32_t n_steps, hipStream_t s)
+hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds, int32_t order,
+                           int32_t precision, int32_t n_steps, hipStream_t s)
 {
     for (int32_t step = 0; step + 1 < n_steps; step += 2)
         for (int dir = 0; dir < 2; ++dir) {
@@ -280,7 +317,7 @@ hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int ro
         }
     if (!(n_steps & 1)) return hipSuccess;
     InstDev J = I;
-    if (rows <= 0) J.rows = launch_rows(J.strips, d.ny, pick_rows(strip_rows_of(d), d.ny, 0));
+    if (rows <= 0) J.rows = launch_rows(J.strips, d.ny, stage_rows_of(d, simds));
     J.chunks = tiles_along_y(d.ny, J.rows);
     int modes[2];
     const int nm = stage_modes(order, 0, modes);

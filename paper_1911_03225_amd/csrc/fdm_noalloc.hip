@@ -131,14 +131,14 @@ extern "C" fdm_status fdm_transport_step_noalloc(const fdm_transport_desc *desc,
     fill_inst(I, d, step_dt(d, smax), stage, stage + (size_t)n * sizeof(float));
     I.a11 = alpha11;
     I.a12 = alpha12;
-    I.rows = pick_rows(strip_rows_of(d), d.ny, 0);
+    I.rows = stage_rows_of(d, simds);
     I.strips = (d.nx + fdm::kStrip - 1) / fdm::kStrip;
     I.fstrips = (d.nx + fdm::kFusedStrip - 1) / fdm::kFusedStrip;
     I.chunks = fdm::tiles_along_y(d.ny, I.rows);
     if (fused_applies(FDM_PRECISION_FP32, order, fd)) {
         I.rows = fused_rows([&](int h) { return (int64_t)I.fstrips * fdm::tiles_along_y(d.ny, h); }, d.ny, simds);
         I.chunks = fdm::tiles_along_y(d.ny, I.rows);
-        e = run_fused_steps(I, d, 0, order, FDM_PRECISION_FP32, n_steps, s);
+        e = run_fused_steps(I, d, 0, simds, order, FDM_PRECISION_FP32, n_steps, s);
         return e == hipSuccess ? FDM_OK : device_error("fused launch", e);
     }
     for (int32_t step = 0; step < n_steps; ++step) {
