@@ -63,6 +63,9 @@ __device__ __forceinline__ double from_right(double v)
     return __hiloint2double(hi, lo);
 }
 
+// both conditions, without a branch
+__device__ __forceinline__ bool both(bool a, bool b) { return (int)a & (int)b; }
+
 // every active lane's condition (a scalar compare of the wave's mask)
 __device__ __forceinline__ bool wave_all(bool c) { return __builtin_amdgcn_ballot_w64(!c) == 0; }
 
@@ -298,20 +301,24 @@ __device__ __forceinline__ R numerical_hamiltonian(R pxm, R pxp, R pym, R pyp, R
         const R g10 = v0 * Arith<R>::rsq(vmax(r10, kTiny));
         const R g11 = v0 * Arith<R>::rsq(vmax(r11, kTiny));
         const R H00 = r00 * g00, H01 = r01 * g01, H10 = r10 * g10, H11 = r11 * g11;
-        const R hx00 = pxm * g00, hx01 = pxm * g01, hx10 = pxp * g10, hx11 = pxp * g11;
-        const R hy00 = pym * g00, hy01 = pyp * g01, hy10 = pym * g10, hy11 = pyp * g11;
         // Step 2: one-sided local speeds over the four combinations, bounded
-        // by +-FLT_MIN instead of 0 (two three-operand max/min each).  Then
+        // by +-FLT_MIN instead of 0 (a three-operand max/min each).  Of the
+        // two combinations of a face value the one with the larger |g| (all
+        // g have the sign of v0) is the larger speed of either sign, so it is
+        // picked first: 2 med3, 2 products and 2 max/min an axis where the
+        // products of all four corners and their max/min took 8, with the
+        // same bits (rounded products are monotone).  Then
         // a+ - a- >= 2 FLT_MIN always: where nothing moves along an axis the
         // weights come out as exactly 1/2 (2^-126 * rcp(2^-125)) and the
         // viscosity as -FLT_MIN/2, which is the scheme's degenerate case up
         // to a term below the smallest normal number per unit gradient jump,
         // with no compare or select; a one-sided speed of 0 becomes 1.2e-38,
         // which moves nothing representable against normal densities.
-        const R ap = vmax(vmax(vmax(vmax(hx00, hx01), hx10), hx11), kTiny);
-        const R am = vmin(vmin(vmin(vmin(hx00, hx01), hx10), hx11), -kTiny);
-        const R bp = vmax(vmax(vmax(vmax(hy00, hy01), hy10), hy11), kTiny);
-        const R bm = vmin(vmin(vmin(vmin(hy00, hy01), hy10), hy11), -kTiny);
+        const R away = sign_inf(v0);
+        const R hxm = pxm * med3(g00, g01, away), hxp = pxp * med3(g10, g11, away);
+        const R hym = pym * med3(g00, g10, away), hyp = pyp * med3(g01, g11, away);
+        const R ap = vmax(vmax(hxm, hxp), kTiny), am = vmin(vmin(hxm, hxp), -kTiny);
+        const R bp = vmax(vmax(hym, hyp), kTiny), bm = vmin(vmin(hym, hyp), -kTiny);
         // Steps 3-4 (dt -> 0): projection weights.  The sum keeps the order
         // of the definition (weighted corner values, then the two viscosity
         // terms): rewriting it, e.g. with w_+ = 1 - w_-, lets FMA
@@ -484,7 +491,7 @@ __device__ __forceinline__ bool numerical_hamiltonian_shared(double pxm, double 
     s += wxp * wym * (v0 * r10);
     s += wxp * wyp * (v0 * r11);
     hhat = s + (visc_x * (pxp - pxm) + visc_y * (pyp - pym));
-    return ok & (fabs(v0) < __builtin_inf());
+    return both(ok, fabs(v0) < __builtin_inf());
 }
 
 // Whether a density lies where the shared evaluation above is exact: any
@@ -534,12 +541,14 @@ __device__ __forceinline__ float fd_hamiltonian(float pxm, float pxp, float pym,
         const float g01 = v0 * Arith<float>::rsq(vmax(madd(pyp, pyp, xm2), kTiny));
         const float g10 = v0 * Arith<float>::rsq(vmax(madd(pym, pym, xp2), kTiny));
         const float g11 = v0 * Arith<float>::rsq(vmax(madd(pyp, pyp, xp2), kTiny));
-        const float hx00 = pxm * g00, hx01 = pxm * g01, hx10 = pxp * g10, hx11 = pxp * g11;
-        const float hy00 = pym * g00, hy01 = pyp * g01, hy10 = pym * g10, hy11 = pyp * g11;
-        ap = vmax(vmax(vmax(vmax(hx00, hx01), hx10), hx11), kTiny);
-        am = vmin(vmin(vmin(vmin(hx00, hx01), hx10), hx11), -kTiny);
-        bp = vmax(vmax(vmax(vmax(hy00, hy01), hy10), hy11), kTiny);
-        bm = vmin(vmin(vmin(vmin(hy00, hy01), hy10), hy11), -kTiny);
+        // the larger speed of each face value, as in numerical_hamiltonian
+        const float away = sign_inf(v0);
+        const float hxm = pxm * med3(g00, g01, away), hxp = pxp * med3(g10, g11, away);
+        const float hym = pym * med3(g00, g10, away), hyp = pyp * med3(g01, g11, away);
+        ap = vmax(vmax(hxm, hxp), kTiny);
+        am = vmin(vmin(hxm, hxp), -kTiny);
+        bp = vmax(vmax(hym, hyp), kTiny);
+        bm = vmin(vmin(hym, hyp), -kTiny);
     }
     // slopes of the interpolant at the intermediate points
     const float qxm = madd(cx * am, sxm, pxm), qxp = madd(cx * ap, sxp, pxp);
@@ -921,7 +930,7 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
                 // rows k-2 .. k+1 of alpha_11 and row k of alpha_12 are the stencil
                 y_out = (y_out << 1 | (wave_all(edge_in_range(y[(p + 1) & 7])) ? 0 : 1)) & 15;
                 const bool ok = numerical_hamiltonian_shared(pxm, pxp, pym, pyp, v0, hv);
-                if (y_out != 0 || !wave_all(ok & edge_in_range(wx_[c])))
+                if (y_out != 0 || !wave_all(both(ok, edge_in_range(wx_[c]))))
                     hv = numerical_hamiltonian_ieee<VH>(pxm, pxp, pym, pyp, v0, V1, V2);
             }
         } else {
@@ -1129,7 +1138,7 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         bool fine = false;
         if constexpr (kShared) {
             const bool ok = numerical_hamiltonian_shared(q[0], q[1], q[2], q[3], v0, hv);
-            fine = out == 0 && wave_all(ok & edge_in_range(wx));
+            fine = out == 0 && wave_all(both(ok, edge_in_range(wx)));
         }
         if (!fine) hv = numerical_hamiltonian_ieee<VK>(q[0], q[1], q[2], q[3], v0, V1, V2);
         return hv;
