@@ -44,8 +44,8 @@ struct fdm_ctx {
     int32_t *d_tile_inst = nullptr;         // batched: tile -> instance
     int64_t total_tiles = 0;
     fdm::StatsPartial *d_partials = nullptr;
-    double *d_stats = nullptr;              // 5 doubles per instance
-    double *h_stats = nullptr;              // pinned copy
+    double *h_stats = nullptr;              // 5 doubles per instance, pinned (the kernels write them)
+    int stats_most = 1;                     // largest number of blocks an instance's diagnostics take
     float *d_absmax = nullptr;
     bool table_valid = false;
     bool have_ref = false;
@@ -180,7 +180,6 @@ void release(fdm_ctx *c)
     if (c->d_inst) (void)hipFree(c->d_inst);
     if (c->d_tile_inst) (void)hipFree(c->d_tile_inst);
     if (c->d_partials) (void)hipFree(c->d_partials);
-    if (c->d_stats) (void)hipFree(c->d_stats);
     if (c->d_absmax) (void)hipFree(c->d_absmax);
     if (c->h_stats) (void)hipHostFree(c->h_stats);
     if (c->h_inst_pinned) (void)hipHostFree(c->h_inst_pinned);
@@ -347,15 +346,26 @@ void advance(fdm_ctx *c, int32_t n)
     }
 }
 
-fdm_status compute_stats(fdm_ctx *c, void *const *a11, void *const *a12, fdm_stats *out)
+// Enqueues the diagnostics of the given arrays into h_stats.
+fdm_status enqueue_stats(fdm_ctx *c, void *const *a11, void *const *a12)
 {
+    if (c->batched) {   // one launch over the table of instances, and one that folds
+        const fdm_status st = bind(c, a11, a12);
+        if (st != FDM_OK) return st;
+        FDM_HIP(c, fdm::launch_stats_batched(c->d_inst, c->n, c->stats_most, c->precision, c->d_partials, c->h_stats,
+                                             c->stream));
+        return FDM_OK;
+    }
     for (int i = 0; i < c->n; ++i) {
         const int64_t n = (int64_t)c->inst[i].nx * c->inst[i].ny;
-        FDM_HIP(c, fdm::launch_stats(a11[i], a12[i], n, c->precision, c->d_partials, c->d_stats + 5 * i, c->stream));
+        FDM_HIP(c, fdm::launch_stats(a11[i], a12[i], n, c->precision, c->d_partials, c->h_stats + 5 * i, c->stream));
     }
-    FDM_HIP(c, hipMemcpyAsync(c->h_stats, c->d_stats, sizeof(double) * 5 * c->n, hipMemcpyDeviceToHost,
-                              c->stream));
-    FDM_HIP(c, hipStreamSynchronize(c->stream));
+    return FDM_OK;
+}
+
+// The records of diagnostics that have arrived.
+fdm_status collect_stats(fdm_ctx *c, fdm_stats *out)
+{
     if (!c->have_ref) {
         c->ref11.resize(c->n);
         c->ref12.resize(c->n);
@@ -387,6 +397,14 @@ fdm_status compute_stats(fdm_ctx *c, void *const *a11, void *const *a12, fdm_sta
     }
     if (bad) return fail(c, FDM_ERR_NONFINITE, "non-finite density values found");
     return FDM_OK;
+}
+
+fdm_status compute_stats(fdm_ctx *c, void *const *a11, void *const *a12, fdm_stats *out)
+{
+    const fdm_status st = enqueue_stats(c, a11, a12);
+    if (st != FDM_OK) return st;
+    FDM_HIP(c, hipStreamSynchronize(c->stream));
+    return collect_stats(c, out);
 }
 
 fdm_status static_fail(fdm_ctx *c, fdm::StaticStatus st, const std::string &err)
@@ -516,7 +534,7 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
                 FDM_HIP(c, fdm::launch_copy(J.a12, J.w12, n, c->precision, s));
             }
         }
-        FDM_HIP(c, fdm::launch_coupled_slip(slip, s));
+        FDM_HIP(c, fdm::launch_coupled_slip(slip, w.h_cd, s));
         return FDM_OK;
     };
 
@@ -574,7 +592,10 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
         }
         done += m;
         c->steps += m;
-        FDM_HIP(c, hipMemcpyAsync(w.h_cd, w.d_cd, sizeof(fdm::CoupledDev), hipMemcpyDeviceToHost, c->stream));
+        if (history) {
+            st = enqueue_stats(c, a11, a12);
+            if (st != FDM_OK) return st;
+        }
         FDM_HIP(c, hipStreamSynchronize(c->stream));
         if (w.h_cd->coef.nonfinite) return fail(c, FDM_ERR_NONFINITE, "non-finite celerity in the coupled run");
         c->t_acc[0] = w.h_cd->t;
@@ -584,7 +605,7 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
         w.sigma13 = w.h_cd->sigma_bar;
         w.vmax = w.h_cd->coef.vmax;
         if (history) {
-            st = compute_stats(c, a11, a12, history + rec);
+            st = collect_stats(c, history + rec);
             if (st != FDM_OK) return st;
             ++rec;
         }
@@ -678,14 +699,20 @@ fdm_status fdm_transport_init(const fdm_transport_desc *descs, int32_t n_instanc
         c->simds = 4 * (int64_t)std::max(cus, 1);
     }
     INIT_HIP(hipMalloc((void **)&c->workspace, elem * total));
-    INIT_HIP(hipMalloc((void **)&c->d_partials, sizeof(fdm::StatsPartial) * fdm::kStatsBlocks));
-    INIT_HIP(hipMalloc((void **)&c->d_stats, sizeof(double) * 5 * n_instances));
+    // diagnostics partials: of every instance side by side (batched), or of one at a time
+    int64_t parts = 0;
+    for (int i = 0; i < n_instances; ++i) {
+        const int b = fdm::stats_blocks((int64_t)descs[i].nx * descs[i].ny);
+        c->stats_most = std::max(c->stats_most, b);
+        parts += b;
+    }
+    INIT_HIP(hipMalloc((void **)&c->d_partials, sizeof(fdm::StatsPartial) * (c->batched ? parts : c->stats_most)));
     INIT_HIP(hipHostMalloc((void **)&c->h_stats, sizeof(double) * 5 * n_instances, hipHostMallocDefault));
     // max |v0| partials: of the celerity field at init, of the velocity law in coupled runs
     INIT_HIP(hipMalloc((void **)&c->d_absmax, sizeof(float) * std::max(fdm::kAbsmaxBlocks, fdm::kLawBlocks)));
 
     std::vector<float> absmax(fdm::kAbsmaxBlocks);
-    int64_t off = 0;
+    int64_t off = 0, first_part = 0;
     for (int i = 0; i < n_instances; ++i) {
         const fdm_transport_desc &d = descs[i];
         const int64_t n = (int64_t)d.nx * d.ny;
@@ -719,6 +746,8 @@ fdm_status fdm_transport_init(const fdm_transport_desc *descs, int32_t n_instanc
         fill_inst(c->inst[i], d, dt, static_cast<char *>(c->workspace) + elem * off,
                   static_cast<char *>(c->workspace) + elem * (off + n));
         off += 2 * n;
+        c->inst[i].stats_first = first_part;
+        first_part += fdm::stats_blocks(n);
     }
     c->dt_last = c->dt;
     {

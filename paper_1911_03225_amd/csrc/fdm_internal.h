@@ -195,6 +195,7 @@ struct InstDev {
     int32_t strips, chunks;  // tiles along x and y
     int32_t fstrips;         // tiles along x of the fused Heun kernel (56 columns)
     int64_t tile_begin;      // first global tile of this instance (batched)
+    int64_t stats_first;     // its first partial of the diagnostics (batched)
     double cxd, cyd, thetad; // the same coefficients for FP64 arithmetic
     double dtd, dxd, dyd;    // step and spacings (FP64 update in definition form)
     double rdxd, rdyd;       // 1/dx, 1/dy, rounded to nearest
@@ -215,7 +216,19 @@ struct StatsPartial {
     double s11, c11, s12, c12, sab, cab, maxn, nonfinite;
 };
 
-constexpr int kStatsBlocks = 512;   // fixed => deterministic reduction order
+// Blocks that sum an instance's diagnostics, by its size alone (so the
+// reduction order is deterministic): one block of 1024 threads does up to
+// 16384 nodes (one launch, no partials: 64^2 5.5 us against 5.7 + 5.3 for 512
+// blocks and their fold), beyond that 2048 nodes a block of 256 threads, at
+// most 512 blocks.
+constexpr int kStatsBlocks = 512;
+constexpr int kStatsSmallThreads = 1024;
+__host__ __device__ inline int stats_blocks(int64_t nodes)
+{
+    if (nodes <= 16 * kStatsSmallThreads) return 1;
+    const int64_t b = (nodes + 2047) / 2048;
+    return b < kStatsBlocks ? (int)b : kStatsBlocks;
+}
 
 hipError_t launch_stage(const InstDev &I, int mode, int precision, hipStream_t s);
 // fd: the instances use the fully discrete scheme (all or none of a batch)
@@ -234,15 +247,20 @@ hipError_t launch_fused_batched(const InstDev *d_inst, const int32_t *d_tile_ins
 // instance back into the states, over the same tile map.
 hipError_t launch_copy_back_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles,
                                     hipStream_t s);
+// out: five doubles (pinned host memory: the kernels write them there).
 hipError_t launch_stats(const void *a11, const void *a12, int64_t n, int precision,
-                        StatsPartial *d_partials, double *d_out, hipStream_t s);
+                        StatsPartial *d_partials, double *out, hipStream_t s);
+// Every instance of the table in two launches; most_blocks: the largest
+// stats_blocks of them; out: five doubles per instance.
+hipError_t launch_stats_batched(const InstDev *d_inst, int n_inst, int most_blocks, int precision,
+                                StatsPartial *d_partials, double *out, hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, int64_t n, int precision, hipStream_t s);
 
 constexpr int kAbsmaxBlocks = 256;
 
 // Coupled runs: the slip update of the last step before the host reads the
-// scalars back (one block; within a chunk the next step's pack kernel runs
-// it).
-hipError_t launch_coupled_slip(const SlipArgs &a, hipStream_t s);
+// scalars (one block, which also copies them to `mirror`, pinned host memory;
+// within a chunk the next step's first kernel runs it).
+hipError_t launch_coupled_slip(const SlipArgs &a, CoupledDev *mirror, hipStream_t s);
 
 }  // namespace fdm

@@ -98,15 +98,16 @@ __device__ __forceinline__ void neumaier(double &s, double &c, double x)
     s = t;
 }
 
+// The diagnostics of one pair of arrays by the blocks 0 .. blocks-1 of a
+// launch; the largest norm is kept as its square (the root of the largest is
+// the largest root, correctly rounded either way).
 template <typename S>
-__global__ __launch_bounds__(256) void stats_partial_kernel(const S *__restrict__ a11,
-                                                            const S *__restrict__ a12, int64_t n,
-                                                            StatsPartial *__restrict__ out)
+__device__ __forceinline__ void stats_sum(const S *__restrict__ a11, const S *__restrict__ a12, int64_t n, int block,
+                                          int blocks, StatsPartial *lds, StatsPartial &p)
 {
-    __shared__ StatsPartial lds[4];
-    StatsPartial p = {0, 0, 0, 0, 0, 0, 0, 0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    p = StatsPartial{0, 0, 0, 0, 0, 0, 0, 0};
+    const int64_t stride = (int64_t)blocks * blockDim.x;
+    for (int64_t i = (int64_t)block * blockDim.x + threadIdx.x; i < n; i += stride) {
         const S x = a11[i], y = a12[i];
         if (!isfinite(x) || !isfinite(y)) {
             p.nonfinite += 1.0;
@@ -116,27 +117,76 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(const S *__restrict_
         neumaier(p.s11, p.c11, dx);
         neumaier(p.s12, p.c12, dy);
         neumaier(p.sab, p.cab, fabs(dx) + fabs(dy));
-        p.maxn = fmax(p.maxn, sqrt(dx * dx + dy * dy));
+        p.maxn = fmax(p.maxn, dx * dx + dy * dy);
     }
     block_reduce(p, lds);
+}
+
+__device__ __forceinline__ void stats_out(const StatsPartial &p, double *out)
+{
+    out[0] = p.s11 + p.c11;
+    out[1] = p.s12 + p.c12;
+    out[2] = p.sab + p.cab;
+    out[3] = sqrt(p.maxn);
+    out[4] = p.nonfinite;
+}
+
+// One block does a small grid alone and writes the five results itself.
+template <typename S>
+__global__ __launch_bounds__(kStatsSmallThreads) void stats_small_kernel(const S *__restrict__ a11,
+                                                                         const S *__restrict__ a12, int64_t n,
+                                                                         double *__restrict__ out)
+{
+    __shared__ StatsPartial lds[kStatsSmallThreads / 64];
+    StatsPartial p;
+    stats_sum<S>(a11, a12, n, 0, 1, lds, p);
+    if (threadIdx.x == 0) stats_out(p, out);
+}
+
+template <typename S>
+__global__ __launch_bounds__(256) void stats_partial_kernel(const S *__restrict__ a11, const S *__restrict__ a12,
+                                                            int64_t n, StatsPartial *__restrict__ out)
+{
+    __shared__ StatsPartial lds[4];
+    StatsPartial p;
+    stats_sum<S>(a11, a12, n, blockIdx.x, gridDim.x, lds, p);
     if (threadIdx.x == 0) out[blockIdx.x] = p;
 }
 
-// One block folds the kStatsBlocks partials in fixed order:
-// out = {sum11, sum12, sum_abs, max_norm, nonfinite}.
-__global__ __launch_bounds__(kStatsBlocks) void stats_final_kernel(const StatsPartial *__restrict__ parts,
+// Every instance of a batch in one launch: row y of the grid is instance y,
+// whose first stats_blocks(nodes) blocks sum it.
+template <typename S>
+__global__ __launch_bounds__(256) void stats_batched_kernel(const InstDev *__restrict__ insts,
+                                                            StatsPartial *__restrict__ out)
+{
+    __shared__ StatsPartial lds[4];
+    const InstDev &I = insts[blockIdx.y];
+    const int64_t n = (int64_t)I.nx * I.ny;
+    const int blocks = stats_blocks(n);
+    if ((int)blockIdx.x >= blocks) return;
+    StatsPartial p;
+    stats_sum<S>(static_cast<const S *>(I.a11), static_cast<const S *>(I.a12), n, blockIdx.x, blocks, lds, p);
+    if (threadIdx.x == 0) out[I.stats_first + blockIdx.x] = p;
+}
+
+// One block folds the partials of one instance in fixed order: out = {sum11,
+// sum12, sum_abs, max_norm, nonfinite}.  insts (a batch) may be null: then
+// `blocks` partials of the one instance.
+__global__ __launch_bounds__(kStatsBlocks) void stats_final_kernel(const StatsPartial *__restrict__ parts, int blocks,
+                                                                   const InstDev *__restrict__ insts,
                                                                    double *__restrict__ out)
 {
     __shared__ StatsPartial lds[kStatsBlocks / 64];
-    StatsPartial p = parts[threadIdx.x];
-    block_reduce(p, lds);
-    if (threadIdx.x == 0) {
-        out[0] = p.s11 + p.c11;
-        out[1] = p.s12 + p.c12;
-        out[2] = p.sab + p.cab;
-        out[3] = p.maxn;
-        out[4] = p.nonfinite;
+    int first = 0;
+    if (insts) {
+        const InstDev &I = insts[blockIdx.x];
+        first = (int)I.stats_first;
+        blocks = stats_blocks((int64_t)I.nx * I.ny);
     }
+    StatsPartial p{0, 0, 0, 0, 0, 0, 0, 0};
+    if ((int)threadIdx.x < blocks) p = parts[first + (int)threadIdx.x];
+    block_reduce(p, lds);
+    if (threadIdx.x == 0) stats_out(p, out + 5 * blockIdx.x);
 }
 
 // Largest |v| per block (NaN if the block saw a non-finite value).  Blocks
@@ -202,18 +252,20 @@ __global__ __launch_bounds__(256) void copy_kernel(S *__restrict__ dst, const S 
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = src[i];
 }
 
-// One block: the slip update of a coupled step.
-__global__ __launch_bounds__(256) void coupled_slip_kernel(SlipArgs a)
+// One block: the slip update of a coupled step, and the step's scalars to
+// the host's pinned mirror.
+__global__ __launch_bounds__(256) void coupled_slip_kernel(SlipArgs a, CoupledDev *mirror)
 {
     __shared__ double2 lds[256];
     coupled_slip_block(a, lds);
+    if (threadIdx.x == 0) *mirror = *a.cd;
 }
 
 }  // namespace
 
-hipError_t launch_coupled_slip(const SlipArgs &a, hipStream_t s)
+hipError_t launch_coupled_slip(const SlipArgs &a, CoupledDev *mirror, hipStream_t s)
 {
-    hipLaunchKernelGGL(coupled_slip_kernel, dim3(1), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(coupled_slip_kernel, dim3(1), dim3(256), 0, s, a, mirror);
     return hipGetLastError();
 }
 
@@ -223,16 +275,38 @@ hipError_t launch_absmax(const float *v, int64_t n, float *d_partial, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_stats(const void *a11, const void *a12, int64_t n, int precision, StatsPartial *d_partials,
-                        double *d_out, hipStream_t s)
+template <typename S>
+static void stats_launches(const void *a11, const void *a12, int64_t n, StatsPartial *parts, double *out, hipStream_t s)
 {
+    const S *x = static_cast<const S *>(a11), *y = static_cast<const S *>(a12);
+    const int blocks = stats_blocks(n);
+    if (blocks == 1) {
+        hipLaunchKernelGGL(stats_small_kernel<S>, dim3(1), dim3(kStatsSmallThreads), 0, s, x, y, n, out);
+        return;
+    }
+    hipLaunchKernelGGL(stats_partial_kernel<S>, dim3(blocks), dim3(256), 0, s, x, y, n, parts);
+    hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(kStatsBlocks), 0, s, (const StatsPartial *)parts, blocks,
+                       (const InstDev *)nullptr, out);
+}
+
+hipError_t launch_stats(const void *a11, const void *a12, int64_t n, int precision, StatsPartial *d_partials,
+                        double *out, hipStream_t s)
+{
+    if (precision == PREC_FP64) stats_launches<double>(a11, a12, n, d_partials, out, s);
+    else stats_launches<float>(a11, a12, n, d_partials, out, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_stats_batched(const InstDev *d_inst, int n_inst, int most_blocks, int precision,
+                                StatsPartial *d_partials, double *out, hipStream_t s)
+{
+    const dim3 grid(most_blocks, n_inst);
     if (precision == PREC_FP64)
-        hipLaunchKernelGGL(stats_partial_kernel<double>, dim3(kStatsBlocks), dim3(256), 0, s,
-                           static_cast<const double *>(a11), static_cast<const double *>(a12), n, d_partials);
+        hipLaunchKernelGGL(stats_batched_kernel<double>, grid, dim3(256), 0, s, d_inst, d_partials);
     else
-        hipLaunchKernelGGL(stats_partial_kernel<float>, dim3(kStatsBlocks), dim3(256), 0, s,
-                           static_cast<const float *>(a11), static_cast<const float *>(a12), n, d_partials);
-    hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(kStatsBlocks), 0, s, d_partials, d_out);
+        hipLaunchKernelGGL(stats_batched_kernel<float>, grid, dim3(256), 0, s, d_inst, d_partials);
+    hipLaunchKernelGGL(stats_final_kernel, dim3(n_inst), dim3(kStatsBlocks), 0, s, (const StatsPartial *)d_partials, 0,
+                       d_inst, out);
     return hipGetLastError();
 }
 
