@@ -61,8 +61,6 @@ struct fdm_ctx {
     struct {
         fdm::StaticPlan *plan = nullptr;
         fdm::StaticParams q{};
-        void *tau = nullptr;                // nx*ny, state type
-        void *phi = nullptr;                // nx*ny, state type (wiggly law)
         float *v0 = nullptr;                // nx*ny celerity of the run
         double *d_hsum = nullptr;           // per-tile sums of Hhat, two stages
         int64_t cap = 0;                    // tiles per stage the sums hold
@@ -185,8 +183,6 @@ void release(fdm_ctx *c)
     if (c->h_inst_pinned) (void)hipHostFree(c->h_inst_pinned);
     if (c->capture) (void)hipStreamDestroy(c->capture);
     fdm::static_plan_destroy(c->cw.plan);
-    if (c->cw.tau) (void)hipFree(c->cw.tau);
-    if (c->cw.phi) (void)hipFree(c->cw.phi);
     if (c->cw.v0) (void)hipFree(c->cw.v0);
     if (c->cw.d_hsum) (void)hipFree(c->cw.d_hsum);
     if (c->cw.d_cd) (void)hipFree(c->cw.d_cd);
@@ -443,26 +439,24 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
     // workspace (kept for later calls; the plan is rebuilt when the cell changes)
     auto &w = c->cw;
     const int64_t n = (int64_t)d.nx * d.ny;
-    const bool f64 = c->precision == FDM_PRECISION_FP64;
     const bool same = w.plan && w.q.nx == q.nx && w.q.ny == q.ny && w.q.dx == q.dx && w.q.mu == q.mu &&
                       w.q.lambda == q.lambda && w.q.h == q.h && w.q.n3 == q.n3 && w.q.f64 == q.f64;
     std::string err;
     if (!same) {
         fdm::static_plan_destroy(w.plan);
         w.plan = nullptr;
-        const fdm::StaticStatus ss = fdm::static_plan_create(q, c->stream, &w.plan, err);
+        const fdm::StaticStatus ss = fdm::static_plan_create(q, false, c->stream, &w.plan, err);
         if (ss != fdm::StaticStatus::Ok) return static_fail(c, ss, err);
         w.q = q;
     }
-    if (!w.tau) FDM_HIP(c, hipMalloc(&w.tau, (f64 ? sizeof(double) : sizeof(float)) * n));
-    if (wiggly && !w.phi) FDM_HIP(c, hipMalloc(&w.phi, (f64 ? sizeof(double) : sizeof(float)) * n));
     const fdm::LawParams law{wiggly, L.tau0, L.mobility, L.tau_y, L.beta, L.mobility_field};
     if (!w.v0) FDM_HIP(c, hipMalloc((void **)&w.v0, sizeof(float) * n));
     InstDev I = c->inst[0];
-    if (c->fused && c->requested_rows <= 0) {
-        // the stage kernels' default tiling, as on a plain context: the per-tile
-        // sums then add in the same order whatever the schedule
-        I.rows = launch_rows(I.strips, d.ny, stage_rows_of(d, c->simds));
+    if (c->requested_rows <= 0) {
+        // one tiling whatever the schedule: the per-tile sums of Hhat (in float
+        // within a tile) add in the same order, so a run's mean slip does not
+        // move with the default heights
+        I.rows = launch_rows(I.strips, d.ny, pick_rows(strip_rows_of(d), d.ny, 0));
         I.chunks = fdm::tiles_along_y(d.ny, I.rows);
     }
     const int64_t tiles = (int64_t)I.strips * I.chunks;
@@ -494,7 +488,7 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
 
     I.v0f = w.v0;
     I.vpart = c->d_absmax;
-    I.nvpart = fdm::velocity_law_blocks(n);
+    I.nvpart = fdm::static_plan_partials(w.plan);
     I.cfl_h = d.cfl * h;
     I.dt_max = L.dt_max;
     // the FP64 fully discrete stage sums node increments, the others Hhat
@@ -504,23 +498,26 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
     const int stages = c->time_order == 1 ? 1 : 2;
     const bool mid = c->time_order == 3;
 
-    // One chunk of m steps on stream s.  Each step: (1) the previous step's
+    // m steps on stream s.  Each step: (1) the previous step's
     // mean slip and loading, run by the first kernel of (2) the stress solve
     // of the current state; the celerity field; (3-4) one transport step with
     // v0 frozen, its step derived by the stage kernels from the velocity
-    // law's max |v0| partials, and per-tile sums of Hhat.  (5) The chunk's
-    // last slip update runs in a kernel of its own, ahead of the host's
-    // read-back.  Only kernels: the chunk replays as a graph.
-    auto enqueue_chunk = [&](int32_t m, hipStream_t s) -> fdm_status {
+    // law's max |v0| partials, and per-tile sums of Hhat.  (5) The last slip
+    // update runs in a kernel of its own, which also writes the scalars to the
+    // pinned mirror the host reads.  Only kernels: the steps replay as a graph.
+    // `first`: the call's first step, whose densities the solve copies where
+    // it reads them (later steps' last stage leaves them there: 3 us a step
+    // at 512^2 for the kernel that did).
+    void *in11 = nullptr, *in12 = nullptr;
+    const bool twice = fdm::static_plan_input(w.plan, &in11, &in12) && stages == 2;
+    auto enqueue_chunk = [&](int32_t m, bool first, hipStream_t s) -> fdm_status {
         InstDev J = I;
         for (int32_t j = 0; j < m; ++j) {
             const fdm::SlipArgs *ps = j > 0 ? &slip : nullptr;
-            fdm::StaticStatus ss =
-                wiggly ? fdm::static_plan_run_phi(w.plan, a11[0], a12[0], w.tau, w.phi, &w.d_cd->sigma_bar,
-                                                  &w.d_cd->phi_mean, ps, s, err)
-                       : fdm::static_plan_run(w.plan, a11[0], a12[0], w.tau, &w.d_cd->sigma_bar, ps, s, err);
-            if (ss != fdm::StaticStatus::Ok) return static_fail(c, ss, err);
-            ss = fdm::velocity_law(w.tau, w.phi, f64, w.v0, n, law, c->d_absmax, s, err);
+            const bool there = twice && !(first && j == 0);
+            const fdm::StaticStatus ss =
+                fdm::static_plan_celerity(w.plan, there ? nullptr : a11[0], there ? nullptr : a12[0], law, w.d_cd, ps,
+                                          w.v0, c->d_absmax, s, err);
             if (ss != fdm::StaticStatus::Ok) return static_fail(c, ss, err);
             J.hsum = w.d_hsum;
             J.coef_out = &w.d_cd->coef;
@@ -528,6 +525,8 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
             J.coef_out = nullptr;
             if (stages == 2) {
                 J.hsum = w.d_hsum + tiles;
+                J.p11 = twice ? in11 : nullptr;
+                J.p12 = twice ? in12 : nullptr;
                 FDM_HIP(c, fdm::launch_stage(J, mid ? fdm::MODE_MID2 : fdm::MODE_HEUN2, c->precision, s));
             } else {
                 FDM_HIP(c, fdm::launch_copy(J.a11, J.w11, n, c->precision, s));
@@ -538,18 +537,24 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
         return FDM_OK;
     };
 
-    // Full chunks replay one captured graph when there are at least two of
-    // them (kernel nodes only; a capture that fails or records anything else
-    // leaves the chunks enqueued one kernel at a time, with the same kernels).
+    // Runs of steps replay one captured graph of kGraphSteps of them (kernel
+    // nodes only; a capture that fails or records anything else leaves the
+    // steps enqueued one kernel at a time, with the same kernels).  A replayed
+    // step saves the host's launches (up to 7 us a step on small grids, 2 at
+    // 512^2), but capturing and instantiating costs 35 to 50 us for each step
+    // of the graph, 5 ms for a chunk of 100 that a run of 400 does not earn
+    // back (58 us a step against 45), so the graph is short and calls too short
+    // for it go without.
+    constexpr int32_t kGraphSteps = 16, kGraphLeast = 160;
     hipGraphExec_t gexec = nullptr;
-    if (n_steps / chunk >= 2 && !w.no_graph) {
+    if (n_steps >= kGraphLeast && chunk >= kGraphSteps && !w.no_graph) {
         FDM_HIP(c, hipStreamSynchronize(c->stream));
         const bool sticky0 = c->sticky;
         const std::string err0 = c->err;
         hipGraph_t g = nullptr;
         bool ok = hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal) == hipSuccess;
         if (ok) {
-            const fdm_status cs = enqueue_chunk(chunk, c->capture);
+            const fdm_status cs = enqueue_chunk(kGraphSteps, false, c->capture);
             ok = hipStreamEndCapture(c->capture, &g) == hipSuccess && cs == FDM_OK && g != nullptr;
         }
         size_t nn = 0;
@@ -584,10 +589,15 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
     int32_t rec = 0;
     for (int32_t done = 0; done < n_steps;) {
         const int32_t m = std::min(chunk, n_steps - done);
-        if (m == chunk && gexec) {
-            FDM_HIP(c, hipGraphLaunch(gexec, c->stream));
-        } else {
-            st = enqueue_chunk(m, c->stream);
+        int32_t left = m;
+        if (done == 0 && gexec) {   // the first step by itself
+            st = enqueue_chunk(1, true, c->stream);
+            if (st != FDM_OK) return st;
+            --left;
+        }
+        for (; gexec && left >= kGraphSteps; left -= kGraphSteps) FDM_HIP(c, hipGraphLaunch(gexec, c->stream));
+        if (left > 0) {
+            st = enqueue_chunk(left, done == 0 && !gexec, c->stream);
             if (st != FDM_OK) return st;
         }
         done += m;
@@ -801,18 +811,9 @@ fdm_status fdm_static_solve(const fdm_static_desc *desc, const void *alpha11, co
     hipStream_t s = (hipStream_t)hip_stream;
     std::string err;
     fdm::StaticPlan *plan = nullptr;
-    fdm::StaticStatus st = fdm::static_plan_create(q, s, &plan, err);
+    fdm::StaticStatus st = fdm::static_plan_create(q, true, s, &plan, err);
     if (st == fdm::StaticStatus::Ok) {
-        const double sbar[2] = {static_mean_stress(*desc, q), desc->phi_mean};
-        const hipError_t ce = hipMemcpyAsync(fdm::static_plan_scalars(plan), sbar, sizeof(sbar),
-                                             hipMemcpyHostToDevice, s);
-        if (ce != hipSuccess) {
-            st = fdm::StaticStatus::Device;
-            err = std::string("hipMemcpyAsync: ") + hipGetErrorString(ce);
-        } else {
-            st = fdm::static_plan_run(plan, alpha11, alpha12, tau13_out, fdm::static_plan_scalars(plan), nullptr, s,
-                                      err);
-        }
+        st = fdm::static_plan_run(plan, alpha11, alpha12, tau13_out, static_mean_stress(*desc, q), s, err);
         const hipError_t e = hipStreamSynchronize(s);
         if (st == fdm::StaticStatus::Ok && e != hipSuccess) {
             st = fdm::StaticStatus::Device;

@@ -208,6 +208,7 @@ struct InstDev {
     const float *vpart;      // the partials, or nullptr (the step in this struct)
     StepCoef *coef_out;      // or nullptr
     int32_t nvpart, pad2;
+    void *p11, *p12;         // HSUM, a step's last stage: a second place for the densities, or nullptr
     double cfl_h, dt_max;    // cfl min(dx, dy), the largest step
 };
 

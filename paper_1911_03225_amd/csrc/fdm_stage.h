@@ -794,6 +794,7 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
     constexpr bool kFD = (VK & VK_FD) != 0;   // fully discrete scheme
     constexpr int VH = VK & 1;                // the Hamiltonian
     constexpr bool kBase = MODE == MODE_HEUN2 || MODE == MODE_MID2;   // also reads the base state
+    constexpr bool kTwice = HSUM && kBase;   // a coupled step's last stage, see InstDev::p11
     const int nx = I.nx, ny = I.ny;
     const void *s12 = MODE == MODE_FWD ? I.a12 : I.w12;
     const void *s11 = MODE == MODE_FWD ? I.a11 : I.w11;
@@ -956,6 +957,7 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
             else nv = madd(-cx, dhx, from);
             if constexpr (MODE == MODE_HEUN2) nv = madd(R(0.5), b12, R(0.5) * nv);
             put(row_ptr<S>(d12, k, nx, it < nrows), off_st, S(nv));
+            if constexpr (kTwice) put(row_ptr<S>(I.p12, k, nx, it < nrows && I.p12 != nullptr), off_st, S(nv));
         }
         {   // y-edge (j, k-1/2): d(alpha_11)/dt = (Hhat_k - Hhat_{k-1})/dy; from the second row on
             R nv;
@@ -965,6 +967,7 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
             else nv = madd(cy, dhy, from);
             if constexpr (MODE == MODE_HEUN2) nv = madd(R(0.5), b11, R(0.5) * nv);
             put(row_ptr<S>(d11, kprev, nx, it > 0), off_st, S(nv));
+            if constexpr (kTwice) put(row_ptr<S>(I.p11, kprev, nx, it > 0 && I.p11 != nullptr), off_st, S(nv));
         }
         kprev = k;
         k = next_row(k, ny);

@@ -22,27 +22,15 @@ struct StaticParams {
 
 struct StaticPlan;
 
-// Builds the multiplier table and the FFT plans (synchronizes s).
-StaticStatus static_plan_create(const StaticParams &q, hipStream_t s, StaticPlan **out, std::string &err);
+// Builds the multiplier table and what the transforms need.  once: for a
+// single solve (rather than every step of a run).
+StaticStatus static_plan_create(const StaticParams &q, bool once, hipStream_t s, StaticPlan **out, std::string &err);
 void static_plan_destroy(StaticPlan *p);
 
-// Enqueues tau13 = layer average of sigma13 for densities (a11, a12) and
-// the mean stress *sigma_bar (a device double, read when the kernel runs)
-// on s.  a11/a12 are read only; tau13 is written.  slip (may be null): a
-// coupled step's pending slip update, run by the first kernel (before
-// anything reads the mean stress or slip).
-StaticStatus static_plan_run(StaticPlan *p, const void *a11, const void *a12, void *tau13, const double *sigma_bar,
-                             const SlipArgs *slip, hipStream_t s, std::string &err);
-
-// As static_plan_run, and also phi (= U^p_13) at the nodes with the mean
-// *phi_mean (a device double), from the same forward transforms.
-StaticStatus static_plan_run_phi(StaticPlan *p, const void *a11, const void *a12, void *tau13, void *phi,
-                                 const double *sigma_bar, const double *phi_mean, const SlipArgs *slip,
-                                 hipStream_t s, std::string &err);
-
-// Two device doubles owned by the plan, for callers that hold the mean
-// stress and slip on the host (upload them before a run).
-double *static_plan_scalars(StaticPlan *p);
+// Enqueues tau13 = layer average of sigma13 for densities (a11, a12) and the
+// mean stress sigma_bar on s.  a11/a12 are read only; tau13 is written.
+StaticStatus static_plan_run(StaticPlan *p, const void *a11, const void *a12, void *tau13, double sigma_bar,
+                             hipStream_t s, std::string &err);
 
 // Celerity at the nodes, written as float32, m = mobility * mfield[i] (mfield
 // may be null):
@@ -53,11 +41,23 @@ struct LawParams {
     double tau0, mobility, tau_y, beta;
     const float *mfield;
 };
-// Also writes one max |v0| partial per block (NaN marks a non-finite value)
-// into partial[0 .. velocity_law_blocks(n)), for the step size.
-constexpr int kLawBlocks = 1024;
-int velocity_law_blocks(int64_t n);
-StaticStatus velocity_law(const void *tau13, const void *phi, bool f64, float *v0, int64_t n, const LawParams &law,
-                          float *partial, hipStream_t s, std::string &err);
+
+// Where a coupled step's solve reads its densities from, if not from the
+// state itself: then the step's last stage also writes there, and
+// static_plan_celerity is called with null densities (the first step of a
+// run passes the state, which is copied there).
+bool static_plan_input(StaticPlan *p, void **a11, void **a12);
+
+// Enqueues a coupled step's celerity field on s: the static solve of the
+// densities with the mean stress and slip of cd (device), phi at the nodes
+// for the wiggly law, and the law.  slip (may be null): the previous step's
+// pending slip update, run ahead of everything that reads the mean stress or
+// slip.  Also writes static_plan_partials(p) partials of max |v0| (NaN marks
+// a non-finite value) for the step size.
+StaticStatus static_plan_celerity(StaticPlan *p, const void *a11, const void *a12, const LawParams &law,
+                                  const CoupledDev *cd, const SlipArgs *slip, float *v0, float *partial,
+                                  hipStream_t s, std::string &err);
+constexpr int kLawBlocks = 1024;   // at most this many partials
+int static_plan_partials(const StaticPlan *p);
 
 }  // namespace fdm
