@@ -18,7 +18,8 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libfdm.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 SOURCES = [os.path.join(HERE, "csrc", f) for f in
-           ("fdm_kernels.hip", "fdm_stage_f32.hip", "fdm_stage_f64.hip", "fdm_fused_f64.hip", "fdm_static.hip", "fdm_host.hip",
+           ("fdm_kernels.hip", "fdm_stage_f32.hip", "fdm_stage_f64.hip", "fdm_fused_f64.hip", "fdm_line.hip",
+            "fdm_static.hip", "fdm_host.hip",
             "fdm_api.hip", "fdm_noalloc.hip")]
 # The stencil kernels are bound by VALU issue, not by registers (at most 78
 # VGPRs with both stages in flight): the scheduler that maximises

@@ -224,6 +224,10 @@ fdm_status bind(fdm_ctx *c, void *const *a11, void *const *a12)
 // Enqueue n_steps on stream s for the bound arrays.
 fdm_status enqueue_steps(fdm_ctx *c, int32_t n_steps, hipStream_t s)
 {
+    if (c->schedule == FDM_SCHEDULE_AUTO && c->n == 1 && c->desc[0].ny == 1 && n_steps >= 2) {
+        FDM_HIP(c, run_line_steps(c->inst[0], c->time_order, c->precision, n_steps, s));
+        return FDM_OK;
+    }
     if (c->fused && !c->batched) {
         for (int i = 0; i < c->n; ++i)
             FDM_HIP(c, run_fused_steps(c->inst[i], c->desc[i], c->requested_rows, c->simds, c->time_order,

@@ -89,6 +89,10 @@ int stage_modes(int32_t order, int32_t step, int modes[2]);
 hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds, int32_t order,
                            int32_t precision, int32_t n_steps, hipStream_t s);
 
+// n_steps >= 2 of a one-row instance by launches of several steps each, an
+// even number of them (the last writes the state).
+hipError_t run_line_steps(const InstDev &I, int32_t order, int32_t precision, int32_t n_steps, hipStream_t s);
+
 // Message of the last failed call without a context (fdm_last_error(NULL)).
 void set_init_error(const std::string &msg);
 

@@ -328,5 +328,17 @@ hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int ro
     return hipSuccess;
 }
 
+hipError_t run_line_steps(const InstDev &I, int32_t order, int32_t precision, int32_t n_steps, hipStream_t s)
+{
+    const int32_t pair = 2 * line_steps(order);
+    const int32_t launches = 2 * (int32_t)(((int64_t)n_steps + pair - 1) / pair);
+    for (int32_t k = 0; k < launches; ++k) {
+        const int32_t steps = n_steps / launches + (k < n_steps % launches ? 1 : 0);
+        const hipError_t e = launch_line(I, order, steps, k & 1, precision, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 }  // namespace host
 }  // namespace fdm

@@ -244,6 +244,11 @@ hipError_t launch_fused(const InstDev &I, int dir, bool mid, int precision, hipS
 // map and tile_begin of the fused tiling).
 hipError_t launch_fused_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles, int dir,
                                 bool mid, hipStream_t s);
+// `steps` (at most line_steps) time steps of a one-row instance in one
+// launch, dir 0 from the state into the stage buffer, dir 1 back; any order,
+// scheme and precision.
+int line_steps(int order);
+hipError_t launch_line(const InstDev &I, int order, int steps, int dir, int precision, hipStream_t s);
 // After an odd number of batched fused steps: the stage buffers of every
 // instance back into the states, over the same tile map.
 hipError_t launch_copy_back_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles,

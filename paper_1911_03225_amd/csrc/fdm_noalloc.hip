@@ -135,6 +135,10 @@ extern "C" fdm_status fdm_transport_step_noalloc(const fdm_transport_desc *desc,
     I.strips = (d.nx + fdm::kStrip - 1) / fdm::kStrip;
     I.fstrips = (d.nx + fdm::kFusedStrip - 1) / fdm::kFusedStrip;
     I.chunks = fdm::tiles_along_y(d.ny, I.rows);
+    if (d.ny == 1 && n_steps >= 2) {
+        e = run_line_steps(I, order, FDM_PRECISION_FP32, n_steps, s);
+        return e == hipSuccess ? FDM_OK : device_error("line launch", e);
+    }
     if (fused_applies(FDM_PRECISION_FP32, order, fd)) {
         I.rows = fused_rows([&](int h) { return (int64_t)I.fstrips * fdm::tiles_along_y(d.ny, h); }, d.ny, simds);
         I.chunks = fdm::tiles_along_y(d.ny, I.rows);
