@@ -43,8 +43,8 @@ FIELD_BYTES = 4
 
 PROFILE_FILE = os.path.join(ROOT, "profiles", "fused_kernel_bands_field_4096_fp32_counters.json")
 LIB_FILE = os.path.join(ROOT, "paper_1911_03225_amd", "libfdm.so")
-HEADLINE_KERNEL = "fused_kernel<3, 0, true, false>"   # minmod, LAW, celerity field, Heun
-HEADLINE_SYMBOL = "_ZN3fdm12_GLOBAL__N_112fused_kernelILi3ELi0ELb1ELb0EEEvNS_7InstDevEliii"
+HEADLINE_KERNEL = "fused_kernel<3, 0, true, false, false, float, float>"   # minmod, LAW, celerity field, Heun
+HEADLINE_SYMBOL = "_ZN3fdm12_GLOBAL__N_112fused_kernelILi3ELi0ELb1ELb0ELb0EffEEvNS_7InstDevEliii"
 # Repeated autotuner runs on one box order heights within about 3% of each
 # other differently; within that the height the counters were taken at is kept.
 PROFILED_HEIGHT_SLACK = 1.03

@@ -7,11 +7,15 @@
 
 namespace fdm {
 
-hipError_t launch_fused_f64(const InstDev &I, int dir, bool mid, bool f64_state, hipStream_t s)
+hipError_t launch_fused_f64(const InstDev &I, int dir, int integ, bool f64_state, hipStream_t s)
 {
+    if (integ == FUSED_TWO_STEPS) return hipErrorInvalidValue;   // float only
+    const bool mid = integ == FUSED_MIDPOINT;
     if (f64_state)
-        return mid ? launch_fused_r<double, double, true>(I, dir, s) : launch_fused_r<double, double, false>(I, dir, s);
-    return mid ? launch_fused_r<double, float, true>(I, dir, s) : launch_fused_r<double, float, false>(I, dir, s);
+        return mid ? launch_fused_r<double, double, FUSED_MIDPOINT>(I, dir, s)
+                   : launch_fused_r<double, double, FUSED_HEUN>(I, dir, s);
+    return mid ? launch_fused_r<double, float, FUSED_MIDPOINT>(I, dir, s)
+               : launch_fused_r<double, float, FUSED_HEUN>(I, dir, s);
 }
 
 }  // namespace fdm

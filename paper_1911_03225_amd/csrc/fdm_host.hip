@@ -139,6 +139,13 @@ bool fused_by_default(const fdm_transport_desc *descs, int32_t n, int32_t precis
 {
     const fdm_transport_desc &d = descs[0];
     const bool fd = d.scheme == FDM_SCHEME_FULLY_DISCRETE;
+    // Two single-stage steps a launch, us a step against a launch each: Euler
+    // with a field 64^2 1.9 / 2.6, 512^2 3.0 / 4.0, 2048^2 13.1 / 15.6, 4096^2
+    // 42 / 71; fully discrete 64^2 2.1 / 2.7, 512^2 3.5 / 4.2, 1009 x 757 6.0 /
+    // 6.3, but 2048^2 17.7 / 17.1 (its arithmetic, 1.2 times as much fused,
+    // bounds it there), 4096^2 61 / 60.
+    if (precision == FDM_PRECISION_FP32 && order == 1)
+        return n == 1 && (!fd || (int64_t)d.nx * d.ny <= (int64_t)1 << 20);
     if (precision == FDM_PRECISION_FP32) return fused_applies(precision, order, fd);
     if (n > 1 || !fused_applies(FDM_PRECISION_FP32, order, fd)) return false;
     const bool field = d.velocity == FDM_VELOCITY_LAW && d.v0_field;
@@ -304,28 +311,43 @@ int stage_modes(int32_t order, int32_t step, int modes[2])
     return 1;
 }
 
-// The same bits either way.  The stage kernels' pair on the last odd step
-// costs no more than a fused launch and the copy of both components back
-// (2048^2: 32 us against 26 + 14; 512^2: 8.1 against 5.6 + 4).
+// The same bits either way.  Two stages a step: a fused launch a step, in
+// pairs; the stage kernels' pair on the last step of an odd count costs no
+// more than a fused launch and the copy of both components back (2048^2: 32 us
+// against 26 + 14; 512^2: 8.1 against 5.6 + 4).
+// One stage a step (float): a fused launch takes two steps, and single steps
+// (in either direction) fill up so that the last launch writes the state: an
+// odd number of fused launches and then single ones back, or an even number.
 hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds, int32_t order,
                            int32_t precision, int32_t n_steps, hipStream_t s)
 {
-    for (int32_t step = 0; step + 1 < n_steps; step += 2)
-        for (int dir = 0; dir < 2; ++dir) {
-            const hipError_t e = launch_fused(I, dir, order == 3, precision, s);
-            if (e != hipSuccess) return e;
-        }
-    if (!(n_steps & 1)) return hipSuccess;
     InstDev J = I;
     if (rows <= 0) J.rows = launch_rows(J.strips, d.ny, stage_rows_of(d, simds));
     J.chunks = tiles_along_y(d.ny, J.rows);
+    hipError_t e = hipSuccess;
+    if (order == 1) {
+        // n mod 4: 0, pairs alone; 1, three singles; 2, two singles; 3, one
+        const int32_t singles = n_steps == 1 ? 1 : n_steps % 4 == 0 ? 0 : 4 - n_steps % 4;
+        const int32_t pairs = (n_steps - singles) / 2;
+        for (int32_t k = 0; k < pairs && e == hipSuccess; ++k) e = launch_fused(I, k & 1, FUSED_TWO_STEPS, precision, s);
+        for (int32_t k = 0; k < singles && e == hipSuccess; ++k)
+            e = launch_stage(J, (pairs + k) & 1 ? MODE_BWD : MODE_FWD, precision, s);
+        if (n_steps == 1) {
+            const int64_t n = (int64_t)I.nx * I.ny;
+            if (e == hipSuccess) e = launch_copy(I.a11, I.w11, n, precision, s);
+            if (e == hipSuccess) e = launch_copy(I.a12, I.w12, n, precision, s);
+        }
+        return e;
+    }
+    const int integ = order == 3 ? FUSED_MIDPOINT : FUSED_HEUN;
+    for (int32_t step = 0; step + 1 < n_steps; step += 2)
+        for (int dir = 0; dir < 2; ++dir)
+            if ((e = launch_fused(I, dir, integ, precision, s)) != hipSuccess) return e;
+    if (!(n_steps & 1)) return hipSuccess;
     int modes[2];
     const int nm = stage_modes(order, 0, modes);
-    for (int m = 0; m < nm; ++m) {
-        const hipError_t e = launch_stage(J, modes[m], precision, s);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    for (int m = 0; m < nm && e == hipSuccess; ++m) e = launch_stage(J, modes[m], precision, s);
+    return e;
 }
 
 hipError_t run_line_steps(const InstDev &I, int32_t order, int32_t precision, int32_t n_steps, hipStream_t s)

@@ -12,13 +12,13 @@ hipError_t launch_stage_f64(const InstDev &I, int mode, bool f64_state, hipStrea
 hipError_t launch_stage_batched_f64(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles,
                                     int mode, bool fd, bool f64_state, hipStream_t s);
 
-hipError_t launch_fused_f32(const InstDev &I, int dir, bool mid, hipStream_t s);
-hipError_t launch_fused_f64(const InstDev &I, int dir, bool mid, bool f64_state, hipStream_t s);
+hipError_t launch_fused_f32(const InstDev &I, int dir, int integ, hipStream_t s);
+hipError_t launch_fused_f64(const InstDev &I, int dir, int integ, bool f64_state, hipStream_t s);
 
-hipError_t launch_fused(const InstDev &I, int dir, bool mid, int precision, hipStream_t s)
+hipError_t launch_fused(const InstDev &I, int dir, int integ, int precision, hipStream_t s)
 {
-    if (precision == PREC_FP32) return launch_fused_f32(I, dir, mid, s);
-    return launch_fused_f64(I, dir, mid, precision == PREC_FP64, s);
+    if (precision == PREC_FP32) return launch_fused_f32(I, dir, integ, s);
+    return launch_fused_f64(I, dir, integ, precision == PREC_FP64, s);
 }
 
 hipError_t launch_stage(const InstDev &I, int mode, int precision, hipStream_t s)

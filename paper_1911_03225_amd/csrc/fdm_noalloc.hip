@@ -124,9 +124,9 @@ extern "C" fdm_status fdm_transport_step_noalloc(const fdm_transport_desc *desc,
         smax = smax_uniform(d);
     }
 
-    // one instance, the default schedule of fdm_transport_init (one fused
-    // launch per step where it applies, else one launch per stage; default
-    // tile height): the same kernels and bits
+    // one instance, the default schedule of fdm_transport_init: several steps
+    // a launch on one row, else fused launches of two stages, at the default
+    // tile height; the same kernels and bits
     InstDev I;
     fill_inst(I, d, step_dt(d, smax), stage, stage + (size_t)n * sizeof(float));
     I.a11 = alpha11;
@@ -139,25 +139,19 @@ extern "C" fdm_status fdm_transport_step_noalloc(const fdm_transport_desc *desc,
         e = run_line_steps(I, order, FDM_PRECISION_FP32, n_steps, s);
         return e == hipSuccess ? FDM_OK : device_error("line launch", e);
     }
-    if (fused_applies(FDM_PRECISION_FP32, order, fd)) {
+    if (fused_by_default(&d, 1, FDM_PRECISION_FP32, order)) {
         I.rows = fused_rows([&](int h) { return (int64_t)I.fstrips * fdm::tiles_along_y(d.ny, h); }, d.ny, simds);
         I.chunks = fdm::tiles_along_y(d.ny, I.rows);
         e = run_fused_steps(I, d, 0, simds, order, FDM_PRECISION_FP32, n_steps, s);
         return e == hipSuccess ? FDM_OK : device_error("fused launch", e);
     }
-    for (int32_t step = 0; step < n_steps; ++step) {
-        int modes[2];
-        const int nm = stage_modes(order, step, modes);
-        for (int k = 0; k < nm; ++k)
-            if ((e = fdm::launch_stage(I, modes[k], fdm::PREC_FP32, s)) != hipSuccess)
-                return device_error("stage launch", e);
-    }
-    // one Euler stage ping-pongs between the state and the stage buffer
-    if (order == 1 && (n_steps & 1)) {
-        if ((e = fdm::launch_copy(alpha11, I.w11, n, fdm::PREC_FP32, s)) != hipSuccess)
-            return device_error("copy", e);
-        if ((e = fdm::launch_copy(alpha12, I.w12, n, fdm::PREC_FP32, s)) != hipSuccess)
-            return device_error("copy", e);
+    // large fully discrete grids: a launch a step, to and from the stage buffer
+    for (int32_t step = 0; step < n_steps; ++step)
+        if ((e = fdm::launch_stage(I, step & 1 ? fdm::MODE_BWD : fdm::MODE_FWD, fdm::PREC_FP32, s)) != hipSuccess)
+            return device_error("stage launch", e);
+    if (n_steps & 1) {
+        if ((e = fdm::launch_copy(alpha11, I.w11, n, fdm::PREC_FP32, s)) != hipSuccess) return device_error("copy", e);
+        if ((e = fdm::launch_copy(alpha12, I.w12, n, fdm::PREC_FP32, s)) != hipSuccess) return device_error("copy", e);
     }
     return FDM_OK;
 }

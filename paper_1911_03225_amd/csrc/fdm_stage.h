@@ -100,6 +100,7 @@ template <> struct Arith<float> {
     static constexpr float tiny = 1.17549435e-38f;   // FLT_MIN
     static __device__ __forceinline__ float rsq(float r) { return __builtin_amdgcn_rsqf(r); }
     static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+    static __device__ __forceinline__ float sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 };
 
 template <> struct Arith<double> {
@@ -145,6 +146,7 @@ template <> struct Arith<F2> {
     static constexpr F2 tiny = F2(Arith<float>::tiny);
     static __device__ __forceinline__ F2 rsq(F2 r) { return F2(Arith<float>::rsq(r.a), Arith<float>::rsq(r.b)); }
     static __device__ __forceinline__ F2 rcp(F2 x) { return F2(Arith<float>::rcp(x.a), Arith<float>::rcp(x.b)); }
+    static __device__ __forceinline__ F2 sqrt(F2 x) { return F2(Arith<float>::sqrt(x.a), Arith<float>::sqrt(x.b)); }
 };
 
 // float arithmetic (one value or a lock-step pair)
@@ -523,56 +525,56 @@ __device__ __forceinline__ bool edge_in_range(double w)
 // cx = dt/dx, cy = dt/dy.  The speeds and weights are those of the
 // semi-discrete scheme (same FLT_MIN bounds); |q| uses the hardware square
 // root (|q| = 0 gives H = 0).
-template <int VH>
-__device__ __forceinline__ float fd_hamiltonian(float pxm, float pxp, float pym, float pyp, float sxm, float sxp,
-                                                float sym, float syp, float v0, float V1, float V2, float cx,
-                                                float cy)
+// (T: float, or a lock-step pair.)
+template <int VH, typename T>
+__device__ __forceinline__ T fd_hamiltonian(T pxm, T pxp, T pym, T pyp, T sxm, T sxp, T sym, T syp, T v0, T V1, T V2,
+                                            T cx, T cy)
 {
-    float ap, am, bp, bm;
+    T ap, am, bp, bm;
     if constexpr (VH == VK_PRESCRIBED) {
-        ap = vmax(V1, Arith<float>::tiny);
-        am = vmin(V1, -Arith<float>::tiny);
-        bp = vmax(V2, Arith<float>::tiny);
-        bm = vmin(V2, -Arith<float>::tiny);
+        ap = vmax(V1, Arith<T>::tiny);
+        am = vmin(V1, -Arith<T>::tiny);
+        bp = vmax(V2, Arith<T>::tiny);
+        bm = vmin(V2, -Arith<T>::tiny);
     } else {
-        constexpr float kTiny = Arith<float>::tiny;
-        const float xm2 = pxm * pxm, xp2 = pxp * pxp;
-        const float g00 = v0 * Arith<float>::rsq(vmax(madd(pym, pym, xm2), kTiny));
-        const float g01 = v0 * Arith<float>::rsq(vmax(madd(pyp, pyp, xm2), kTiny));
-        const float g10 = v0 * Arith<float>::rsq(vmax(madd(pym, pym, xp2), kTiny));
-        const float g11 = v0 * Arith<float>::rsq(vmax(madd(pyp, pyp, xp2), kTiny));
+        constexpr T kTiny = Arith<T>::tiny;
+        const T xm2 = pxm * pxm, xp2 = pxp * pxp;
+        const T g00 = v0 * Arith<T>::rsq(vmax(madd(pym, pym, xm2), kTiny));
+        const T g01 = v0 * Arith<T>::rsq(vmax(madd(pyp, pyp, xm2), kTiny));
+        const T g10 = v0 * Arith<T>::rsq(vmax(madd(pym, pym, xp2), kTiny));
+        const T g11 = v0 * Arith<T>::rsq(vmax(madd(pyp, pyp, xp2), kTiny));
         // the larger speed of each face value, as in numerical_hamiltonian
-        const float away = sign_inf(v0);
-        const float hxm = pxm * med3(g00, g01, away), hxp = pxp * med3(g10, g11, away);
-        const float hym = pym * med3(g00, g10, away), hyp = pyp * med3(g01, g11, away);
+        const T away = sign_inf(v0);
+        const T hxm = pxm * med3(g00, g01, away), hxp = pxp * med3(g10, g11, away);
+        const T hym = pym * med3(g00, g10, away), hyp = pyp * med3(g01, g11, away);
         ap = vmax(vmax(hxm, hxp), kTiny);
         am = vmin(vmin(hxm, hxp), -kTiny);
         bp = vmax(vmax(hym, hyp), kTiny);
         bm = vmin(vmin(hym, hyp), -kTiny);
     }
     // slopes of the interpolant at the intermediate points
-    const float qxm = madd(cx * am, sxm, pxm), qxp = madd(cx * ap, sxp, pxp);
-    const float qym = madd(cy * bm, sym, pym), qyp = madd(cy * bp, syp, pyp);
-    float H00, H01, H10, H11;
+    const T qxm = madd(cx * am, sxm, pxm), qxp = madd(cx * ap, sxp, pxp);
+    const T qym = madd(cy * bm, sym, pym), qyp = madd(cy * bp, syp, pyp);
+    T H00, H01, H10, H11;
     if constexpr (VH == VK_PRESCRIBED) {
         H00 = madd(V2, qym, V1 * qxm);
         H01 = madd(V2, qyp, V1 * qxm);
         H10 = madd(V2, qym, V1 * qxp);
         H11 = madd(V2, qyp, V1 * qxp);
     } else {
-        const float xm2 = qxm * qxm, xp2 = qxp * qxp;
-        H00 = v0 * __builtin_amdgcn_sqrtf(madd(qym, qym, xm2));
-        H01 = v0 * __builtin_amdgcn_sqrtf(madd(qyp, qyp, xm2));
-        H10 = v0 * __builtin_amdgcn_sqrtf(madd(qym, qym, xp2));
-        H11 = v0 * __builtin_amdgcn_sqrtf(madd(qyp, qyp, xp2));
+        const T xm2 = qxm * qxm, xp2 = qxp * qxp;
+        H00 = v0 * Arith<T>::sqrt(madd(qym, qym, xm2));
+        H01 = v0 * Arith<T>::sqrt(madd(qyp, qyp, xm2));
+        H10 = v0 * Arith<T>::sqrt(madd(qym, qym, xp2));
+        H11 = v0 * Arith<T>::sqrt(madd(qyp, qyp, xp2));
     }
-    const float ia = Arith<float>::rcp(ap - am), ib = Arith<float>::rcp(bp - bm);
-    const float wxm = ap * ia, wxp = -am * ia;
-    const float wym = bp * ib, wyp = -bm * ib;
-    const float nvx = ap * wxp, nvy = bp * wyp;   // minus the viscosities
-    const float corr_x = madd(0.5f * cx, madd(ap, sxp, -(am * sxm)), pxp - pxm);
-    const float corr_y = madd(0.5f * cy, madd(bp, syp, -(bm * sym)), pyp - pym);
-    const float sum = madd(wxp, madd(wyp, H11, wym * H10), wxm * madd(wyp, H01, wym * H00));
+    const T ia = Arith<T>::rcp(ap - am), ib = Arith<T>::rcp(bp - bm);
+    const T wxm = ap * ia, wxp = -am * ia;
+    const T wym = bp * ib, wyp = -bm * ib;
+    const T nvx = ap * wxp, nvy = bp * wyp;   // minus the viscosities
+    const T corr_x = madd(T(0.5f) * cx, madd(ap, sxp, -(am * sxm)), pxp - pxm);
+    const T corr_y = madd(T(0.5f) * cy, madd(bp, syp, -(bm * sym)), pyp - pym);
+    const T sum = madd(wxp, madd(wyp, H11, wym * H10), wxm * madd(wyp, H01, wym * H00));
     return madd(-nvy, corr_y, madd(-nvx, corr_x, sum));
 }
 
@@ -1015,6 +1017,10 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
 // updates), so the result is the same bit for bit.  Reads src, writes dst
 // (distinct buffers: neighbouring tiles still read src).
 //
+// Two steps of a single-stage integrator (forward Euler, or the fully
+// discrete scheme, float) fuse the same way, the second on the first's
+// densities: half the launches and half the state's traffic.
+//
 // float: the two stages' nodes of an iteration in lock step (F2).  FP64: one
 // after the other, each with its own fall-back to the definition's form; in
 // lock step the registers of both (200) left two waves per SIMD and 4096^2
@@ -1025,11 +1031,15 @@ constexpr int kFStrip = kFusedStrip, kFHalo = 4;
 constexpr int kFAhead = 2;
 static_assert(kFAhead >= 1 && kFAhead <= 5, "fused look-ahead must fit the eight-slot rings");
 
-template <typename R, typename S, int LK, int VK, bool FIELD, bool MID>
+template <typename R, typename S, int LK, int VK, bool FIELD, int INTEG>
 __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int chunk, int lane, const void *src11,
                                                const void *src12, void *dst11, void *dst12)
 {
     constexpr bool kF64 = sizeof(R) == 8;
+    constexpr bool MID = INTEG == FUSED_MIDPOINT, kTwoSteps = INTEG == FUSED_TWO_STEPS;
+    constexpr bool kFD = (VK & VK_FD) != 0;   // (two steps only)
+    constexpr int VH = VK & 1;
+    static_assert(!kFD || (kTwoSteps && !kF64), "the fully discrete scheme fuses two float steps");
     constexpr bool kShared = kF64 && VK == VK_LAW;   // the shared-reciprocal evaluation applies
     const int nx = I.nx, ny = I.ny;
     const R theta = kF64 ? R(I.thetad) : R(I.theta);
@@ -1119,7 +1129,11 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         const T sx = limited_slope<LK>(wl, wx, wr, T(theta));
         const T pxp = madd(T(-0.5f), sx, wx);
         const T pxm = from_left(madd(T(0.5f), sx, wx));
-        return numerical_hamiltonian<VK>(pxm, pxp, pym, pyp, v0, T(V1), T(V2));
+        if constexpr (kFD)
+            return fd_hamiltonian<VH>(pxm, pxp, pym, pyp, from_left(sx), sx, -slhp, -s0, v0, T(V1), T(V2), T(cx),
+                                      T(cy));
+        else
+            return numerical_hamiltonian<VH>(pxm, pxp, pym, pyp, v0, T(V1), T(V2));
     };
 
     // FP64: the slope and the four face values (x -, x +, y -, y +) of a node.
@@ -1143,7 +1157,7 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
             const bool ok = numerical_hamiltonian_shared(q[0], q[1], q[2], q[3], v0, hv);
             fine = out == 0 && wave_all(both(ok, edge_in_range(wx)));
         }
-        if (!fine) hv = numerical_hamiltonian_ieee<VK>(q[0], q[1], q[2], q[3], v0, V1, V2);
+        if (!fine) hv = numerical_hamiltonian_ieee<VH>(q[0], q[1], q[2], q[3], v0, V1, V2);
         return hv;
     };
 
@@ -1160,7 +1174,7 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
     };
     // B's outputs: alpha_12 of row kB and alpha_11 of the row above.  Heun:
     // the mean of the state and one more stage; midpoint: the state plus a
-    // full step.
+    // full step; two single-stage steps: one more stage.
     auto update_b = [&](auto phase, int it, R hv, R hr, R wx, R ym1, R b12, R b11) {
         constexpr int p = decltype(phase)::value;
         constexpr int h = p & 1, hp = h ^ 1;
@@ -1170,12 +1184,12 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         hhB[h] = hv;
         {
             R nv = kF64 ? (MID ? b12 : wx) + cx * -dx : madd(-cx, dx, MID ? b12 : wx);
-            if constexpr (!MID) nv = madd(R(0.5), b12, R(0.5) * nv);
+            if constexpr (!MID && !kTwoSteps) nv = madd(R(0.5), b12, R(0.5) * nv);
             put(row_ptr<S>(dst12, kB, nx, bi < nrows), off_st, S(nv));
         }
         {
             R nv = madd(cy, dy, MID ? b11 : ym1);
-            if constexpr (!MID) nv = madd(R(0.5), b11, R(0.5) * nv);
+            if constexpr (!MID && !kTwoSteps) nv = madd(R(0.5), b11, R(0.5) * nv);
             put(row_ptr<S>(dst11, kBprev, nx, bi > 0), off_st, S(nv));
         }
         kBprev = kB;
@@ -1382,23 +1396,24 @@ hipError_t launch_stage_t(const InstDev &I, int mode, hipStream_t s)
     return hipGetLastError();
 }
 
-// Fused Heun step: dir 0 reads the state and writes the stage buffer, dir 1
-// the other way round.
-template <typename R, typename S, int LK, int VK, bool FIELD, bool MID>
+// Fused Heun or midpoint step, or two single-stage steps: dir 0 reads the state
+// and writes the stage buffer, dir 1 the other way round.
+template <int LK, int VK, bool FIELD, bool MID, bool TWO, typename R, typename S>
 __global__ __launch_bounds__(kBlock) void fused_kernel(InstDev I, int64_t total_tiles, int blocks_per_xcd,
                                                        int strips, int dir)
 {
+    constexpr int INTEG = TWO ? FUSED_TWO_STEPS : MID ? FUSED_MIDPOINT : FUSED_HEUN;
     const int64_t tile = xcd_tile(blocks_per_xcd);
     if (tile >= total_tiles) return;
     const int t = (int)tile;
     const void *s11 = dir ? I.w11 : I.a11, *s12 = dir ? I.w12 : I.a12;
     void *d11 = dir ? I.a11 : I.w11, *d12 = dir ? I.a12 : I.w12;
-    run_tile_fused<R, S, LK, VK, FIELD, MID>(I, t % strips, t / strips, threadIdx.x & 63, s11, s12, d11, d12);
+    run_tile_fused<R, S, LK, VK, FIELD, INTEG>(I, t % strips, t / strips, threadIdx.x & 63, s11, s12, d11, d12);
 }
 
 // Batched fused step: one launch for the fused tiles of every instance;
 // limiter, Hamiltonian and field presence are per instance (wave-uniform).
-template <int DIR, bool MID>
+template <int DIR, int INTEG>
 __global__ __launch_bounds__(kBlock) void fused_kernel_batched(const InstDev *__restrict__ insts,
                                                                const int32_t *__restrict__ tile_inst,
                                                                int64_t total_tiles, int blocks_per_xcd)
@@ -1413,33 +1428,39 @@ __global__ __launch_bounds__(kBlock) void fused_kernel_batched(const InstDev *__
     void *d11 = DIR ? I.a11 : I.w11, *d12 = DIR ? I.a12 : I.w12;
     with_limiter<true>(I.limiter, [&](auto t) {
         constexpr int L = decltype(t)::value;
-        if (I.vkind == VK_PRESCRIBED) run_tile_fused<float, float, L, VK_PRESCRIBED, false, MID>(I, strip, chunk, lane, s11, s12, d11, d12);
-        else if (I.v0f != nullptr) run_tile_fused<float, float, L, VK_LAW, true, MID>(I, strip, chunk, lane, s11, s12, d11, d12);
-        else run_tile_fused<float, float, L, VK_LAW, false, MID>(I, strip, chunk, lane, s11, s12, d11, d12);
+        if (I.vkind == VK_PRESCRIBED) run_tile_fused<float, float, L, VK_PRESCRIBED, false, INTEG>(I, strip, chunk, lane, s11, s12, d11, d12);
+        else if (I.v0f != nullptr) run_tile_fused<float, float, L, VK_LAW, true, INTEG>(I, strip, chunk, lane, s11, s12, d11, d12);
+        else run_tile_fused<float, float, L, VK_LAW, false, INTEG>(I, strip, chunk, lane, s11, s12, d11, d12);
     });
 }
 
-template <typename R, typename S, int LK, int VK, bool FIELD, bool MID>
+template <typename R, typename S, int LK, int VK, bool FIELD, int INTEG>
 hipError_t launch_fused_t(const InstDev &I, int dir, hipStream_t s)
 {
     const int strips = (I.nx + kFStrip - 1) / kFStrip;
     const int64_t tiles = (int64_t)strips * tiles_along_y(I.ny, I.rows);
     const int64_t blocks = (tiles + kWavesPerBlock - 1) / kWavesPerBlock;
     const int per_xcd = (int)((blocks + 7) / 8);
-    hipLaunchKernelGGL((fused_kernel<R, S, LK, VK, FIELD, MID>), dim3(8 * per_xcd), dim3(kBlock), 0, s, I, tiles, per_xcd,
-                       strips, dir);
+    hipLaunchKernelGGL((fused_kernel<LK, VK, FIELD, INTEG == FUSED_MIDPOINT, INTEG == FUSED_TWO_STEPS, R, S>),
+                       dim3(8 * per_xcd), dim3(kBlock), 0, s, I, tiles, per_xcd, strips, dir);
     return hipGetLastError();
 }
 
-template <typename R, typename S, bool MID>
+template <typename R, typename S, int INTEG>
 hipError_t launch_fused_r(const InstDev &I, int dir, hipStream_t s)
 {
-    if (I.vkind != VK_LAW && I.vkind != VK_PRESCRIBED) return hipErrorInvalidValue;   // semi-discrete scheme only
+    constexpr bool kFD = INTEG == FUSED_TWO_STEPS && sizeof(R) == 4;   // the fully discrete scheme has instances
+    if (!kFD && I.vkind != VK_LAW && I.vkind != VK_PRESCRIBED) return hipErrorInvalidValue;
     return with_limiter<sizeof(R) == 4>(I.limiter, [&](auto t) -> hipError_t {
         constexpr int L = decltype(t)::value;
-        if (I.vkind == VK_PRESCRIBED) return launch_fused_t<R, S, L, VK_PRESCRIBED, false, MID>(I, dir, s);
-        if (I.v0f != nullptr) return launch_fused_t<R, S, L, VK_LAW, true, MID>(I, dir, s);
-        return launch_fused_t<R, S, L, VK_LAW, false, MID>(I, dir, s);
+        if constexpr (kFD) {
+            if (I.vkind == VK_PRESCRIBED_FD) return launch_fused_t<R, S, L, VK_PRESCRIBED_FD, false, INTEG>(I, dir, s);
+            if (I.vkind == VK_LAW_FD && I.v0f) return launch_fused_t<R, S, L, VK_LAW_FD, true, INTEG>(I, dir, s);
+            if (I.vkind == VK_LAW_FD) return launch_fused_t<R, S, L, VK_LAW_FD, false, INTEG>(I, dir, s);
+        }
+        if (I.vkind == VK_PRESCRIBED) return launch_fused_t<R, S, L, VK_PRESCRIBED, false, INTEG>(I, dir, s);
+        if (I.v0f != nullptr) return launch_fused_t<R, S, L, VK_LAW, true, INTEG>(I, dir, s);
+        return launch_fused_t<R, S, L, VK_LAW, false, INTEG>(I, dir, s);
     });
 }
 

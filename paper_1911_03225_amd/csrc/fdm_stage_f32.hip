@@ -15,9 +15,13 @@ hipError_t launch_stage_f32(const InstDev &I, int mode, hipStream_t s)
     return launch_stage_r<float, float>(I, mode, s);
 }
 
-hipError_t launch_fused_f32(const InstDev &I, int dir, bool mid, hipStream_t s)
+hipError_t launch_fused_f32(const InstDev &I, int dir, int integ, hipStream_t s)
 {
-    return mid ? launch_fused_r<float, float, true>(I, dir, s) : launch_fused_r<float, float, false>(I, dir, s);
+    switch (integ) {
+    case FUSED_HEUN: return launch_fused_r<float, float, FUSED_HEUN>(I, dir, s);
+    case FUSED_MIDPOINT: return launch_fused_r<float, float, FUSED_MIDPOINT>(I, dir, s);
+    default: return launch_fused_r<float, float, FUSED_TWO_STEPS>(I, dir, s);
+    }
 }
 
 hipError_t launch_fused_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles, int dir,
@@ -28,17 +32,17 @@ hipError_t launch_fused_batched(const InstDev *d_inst, const int32_t *d_tile_ins
     const dim3 grid(8 * per_xcd), block(kBlock);
     if (mid) {
         if (dir)
-            hipLaunchKernelGGL((fused_kernel_batched<1, true>), grid, block, 0, s, d_inst, d_tile_inst, total_tiles,
+            hipLaunchKernelGGL((fused_kernel_batched<1, FUSED_MIDPOINT>), grid, block, 0, s, d_inst, d_tile_inst, total_tiles,
                                per_xcd);
         else
-            hipLaunchKernelGGL((fused_kernel_batched<0, true>), grid, block, 0, s, d_inst, d_tile_inst, total_tiles,
+            hipLaunchKernelGGL((fused_kernel_batched<0, FUSED_MIDPOINT>), grid, block, 0, s, d_inst, d_tile_inst, total_tiles,
                                per_xcd);
     } else {
         if (dir)
-            hipLaunchKernelGGL((fused_kernel_batched<1, false>), grid, block, 0, s, d_inst, d_tile_inst, total_tiles,
+            hipLaunchKernelGGL((fused_kernel_batched<1, FUSED_HEUN>), grid, block, 0, s, d_inst, d_tile_inst, total_tiles,
                                per_xcd);
         else
-            hipLaunchKernelGGL((fused_kernel_batched<0, false>), grid, block, 0, s, d_inst, d_tile_inst, total_tiles,
+            hipLaunchKernelGGL((fused_kernel_batched<0, FUSED_HEUN>), grid, block, 0, s, d_inst, d_tile_inst, total_tiles,
                                per_xcd);
     }
     return hipGetLastError();

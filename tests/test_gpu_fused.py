@@ -351,3 +351,27 @@ def test_auto_batched_odd_steps_bitwise(fdm, steps):
         fdm.fdm_destroy(ctx)
         out.append([t.cpu().numpy() for t in t11 + t12])
     assert all(np.array_equal(x, y) for x, y in zip(*out))
+
+
+@pytest.mark.parametrize("nx,ny", [(1, 2), (64, 64), (57, 3), (300, 200), (513, 130), (1100, 960)])
+@pytest.mark.parametrize("kind", ["uniform", "field", "prescribed"])
+@pytest.mark.parametrize("scheme", ["semidiscrete", "fully_discrete"])
+def test_two_single_stage_steps_a_launch_bitwise(fdm, nx, ny, kind, scheme):
+    """AUTO takes two Euler (or fully discrete) steps a launch and fills up
+    with single ones, for every remainder of the count and both buffers: the
+    plain schedule's bits; the allocation-free entry the same."""
+    rng = np.random.default_rng(nx + 7 * ny)
+    a11, a12 = (rng.standard_normal((ny, nx)).astype(np.float32) for _ in range(2))
+    kw = dict(limiter="superbee", cfl=0.25, time_order=1, scheme=scheme, dx=0.5, dy=0.5)
+    kw.update({"uniform": dict(v0=-0.8), "field": dict(v0_field=rng.uniform(-1, 1, (ny, nx)).astype(np.float32)),
+               "prescribed": dict(velocity="prescribed", V=(0.6, -0.9))}[kind])
+    _, p = gpu_run(a11, a12, 9, snapshots=list(range(1, 10)), options={"schedule": "plain"}, **dict(kw))
+    for steps in (1, 2, 3, 4, 5, 6, 9):
+        _, a = gpu_run(a11, a12, steps, **dict(kw))
+        assert np.array_equal(a[-1][1], p[steps - 1][1]) and np.array_equal(a[-1][2], p[steps - 1][2]), steps
+    if kind != "field":
+        import torch
+        t11, t12 = to_dev(a11), to_dev(a12)
+        fdm.fdm_transport_step_noalloc(fdm.desc(nx, ny, **kw), t11, t12, 7)
+        torch.cuda.synchronize()
+        assert np.array_equal(t11.cpu().numpy(), p[6][1]) and np.array_equal(t12.cpu().numpy(), p[6][2])
