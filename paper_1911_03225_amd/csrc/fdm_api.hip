@@ -929,12 +929,14 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
     int max_ny = 0;
     for (int i = 0; i < c->n; ++i) max_ny = std::max(max_ny, c->desc[i].ny);
     // candidate schedules: the requested one, or under AUTO batched and plain
-    // (several instances) and the fused Heun launches where they apply
+    // (several instances) and the fused launches where float ones apply or
+    // AUTO takes them by itself
     std::vector<int> schedules;
     if (c->schedule == FDM_SCHEDULE_AUTO) {
         if (c->n > 1) schedules = {FDM_SCHEDULE_BATCHED, FDM_SCHEDULE_PLAIN};
         else schedules = {FDM_SCHEDULE_PLAIN};
-        if (fused_applies(c->precision, c->time_order, c->fd))
+        if (fused_applies(c->precision, c->time_order, c->fd) ||
+            fused_by_default(c->desc.data(), c->n, c->precision, c->time_order))
             schedules.push_back(FDM_SCHEDULE_FUSED);
     } else {
         schedules = {was_fused ? FDM_SCHEDULE_FUSED : was_batched ? FDM_SCHEDULE_BATCHED : FDM_SCHEDULE_PLAIN};
