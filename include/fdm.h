@@ -142,11 +142,15 @@ typedef struct fdm_transport_desc {
 
 /* Scheduling options; pass NULL for the defaults. */
 typedef enum fdm_schedule {
-    FDM_SCHEDULE_AUTO = 0,     /* one fused launch per step where it is faster
-                                  (FP32: wherever FUSED applies; one instance
-                                  in the FP64 modes: beyond the on-chip cache),
-                                  else batched launches when n_instances > 1,
-                                  else plain                                   */
+    FDM_SCHEDULE_AUTO = 0,     /* the fastest that applies: for one instance of
+                                  one row, several steps a launch; one fused
+                                  launch per step (FP32: wherever FUSED applies;
+                                  one instance in the FP64 modes: beyond the
+                                  on-chip cache); for one FP32 instance with
+                                  single-stage steps, two of them in a fused
+                                  launch (FULLY_DISCRETE: up to 2^20 nodes); else
+                                  batched launches when n_instances > 1, else
+                                  plain                                        */
     FDM_SCHEDULE_BATCHED = 1,  /* one launch per stage for all instances       */
     FDM_SCHEDULE_PLAIN = 2,    /* one launch per stage per instance            */
     FDM_SCHEDULE_FUSED = 3     /* one launch per step (for all instances of a
@@ -190,14 +194,15 @@ typedef enum fdm_precision {
 
 typedef struct fdm_options {
     int32_t schedule;        /* fdm_schedule                                    */
-    int32_t tile_rows;       /* rows per wave tile; 0 picks a default (fused
-                                launches under AUTO: by a model of the launch
-                                time, 1 to 64 rows; FUSED: at most five waves
-                                per SIMD where that gives 4 to 64 rows); doubled until one instance's
-                                launch has at most 2^25 tiles (at the default
-                                heights only grids of at most three columns
-                                and over 2^29 rows need it); results do not
-                                depend on it                                  */
+    int32_t tile_rows;       /* rows per wave tile; 0 picks a default (AUTO's
+                                fused launches: by a model of the launch time,
+                                1 to 64 rows; FUSED: at most five waves per
+                                SIMD where that gives 4 to 64 rows; stage
+                                launches: the height that evens the SIMDs out);
+                                doubled until one instance's launch has at most
+                                2^25 tiles (at the default heights only grids
+                                of at most three columns and over 2^29 rows
+                                need it); results do not depend on it         */
     int32_t fused;           /* reserved, must be 0                             */
     int32_t precision;       /* fdm_precision                                   */
 } fdm_options;
@@ -288,9 +293,10 @@ typedef struct fdm_static_desc {
 
 /* Writes tau13_out[k*nx + j] at the nodes.  alpha11/alpha12/tau13_out are
  * device arrays of nx*ny floats (doubles in FP64 precision), distinct; the
- * densities are read only.  Builds the FFT plans and the multiplier table
- * for the call, runs on hip_stream and returns after the result is complete
- * (synchronous).  Errors: FDM_ERR_INVALID_ARG (checked on the host first),
+ * densities are read only.  Builds the transforms' tables (or the FFT plans,
+ * where a line is too long for the on-chip transforms or has a large prime
+ * factor) and the multiplier table for the call, runs on hip_stream and
+ * returns after the result is complete (synchronous).  Errors: FDM_ERR_INVALID_ARG (checked on the host first),
  * FDM_ERR_OUT_OF_MEMORY, FDM_ERR_DEVICE (message in fdm_last_error(NULL)). */
 fdm_status fdm_static_solve(const fdm_static_desc *desc, const void *alpha11,
                             const void *alpha12, void *tau13_out, void *hip_stream);
@@ -354,14 +360,14 @@ typedef struct fdm_loading {
  * descriptor) and dx == dy; the descriptor's v0 / v0_field are not used
  * during the run (they are again after it).  The step size, mean slip and
  * mean stress are computed on the device, so steps are enqueued without
- * waiting; with two full chunks or more, they are replayed from a HIP graph
- * captured once per call (where the FFT library's launches can be captured
- * as kernels; otherwise the same kernels are enqueued directly), and the
- * stream is synchronized
- * once per chunk (to read those scalars back, and for the stats record).
+ * waiting; a call of 160 steps or more whose chunks hold at least 16 replays
+ * them from a HIP graph of 16 steps captured once per call (where the
+ * launches can be captured as kernels; otherwise, and for what is left of a
+ * chunk, the same kernels are enqueued directly), and the stream is
+ * synchronized once per chunk (for those scalars and the stats record).
  * Results do not depend on the chunk length.  The first call allocates the
- * coupled workspace (FFT plans, a stress and a celerity field, per-tile
- * sums), kept until fdm_destroy. */
+ * coupled workspace (transform tables or FFT plans, spectra, a stress and a
+ * celerity field, per-tile sums), kept until fdm_destroy. */
 fdm_status fdm_run(fdm_ctx *ctx, const fdm_loading *loading, void *const *alpha11,
                    void *const *alpha12, int32_t n_steps, int32_t chunk,
                    fdm_stats *history);
@@ -391,8 +397,8 @@ typedef struct fdm_tune_trial {
  * so that the SIMDs carry equal work; and, for a context created with
  * FDM_SCHEDULE_AUTO,
  * for each schedule that applies: batched and plain (several instances),
- * and fused (FP32 precision, time_order 2 or 3, semi-discrete scheme).  Each
- * candidate is timed twice; the three fastest are then timed three more
+ * and fused (FP32 precision, time_order 2 or 3, semi-discrete scheme, or
+ * wherever AUTO itself takes fused launches).  Each candidate is timed twice; the three fastest are then timed three more
  * times each, interleaved, and the context keeps the fastest of them.  alpha11/alpha12 are read, never
  * written; the step count and diagnostics baseline are unchanged.  Up to
  * max_trials measured candidates are written to trials (may be NULL when
