@@ -29,6 +29,9 @@ enum : int { LIM_NONE = 0, LIM_MINMOD = 1, LIM_MC = 2, LIM_THETA = 3, LIM_SUPERB
 // Hamiltonian kind (bit 0: LAW or PRESCRIBED) and scheme (bit 1: the fully
 // discrete scheme of sec. 3.2.3 instead of its dt -> 0 limit).
 enum : int { VK_LAW = 0, VK_PRESCRIBED = 1, VK_FD = 2, VK_LAW_FD = 2, VK_PRESCRIBED_FD = 3 };
+// Kernel kinds only (never InstDev::vkind): LAW with the uniform celerity +1 or
+// -1, which every problem in units of its front speed has.
+enum : int { VK_PLUS_ONE = 4, VK_MINUS_ONE = 8 };
 
 // What one stage launch reads and writes.
 //   MODE_FWD   : w = a + dt L(a)                 (first stage / Euler step)

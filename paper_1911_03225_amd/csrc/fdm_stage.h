@@ -789,6 +789,17 @@ __device__ __forceinline__ void halve_step(InstDev &I)
 }
 
 
+// The uniform celerity; a constant for the kinds +1 and -1, where the products
+// with it (four a node-stage, the fully discrete scheme eight) fall away with
+// the same bits.  See with_uniform for what that measured.
+template <int VK, typename R>
+__device__ __forceinline__ R uniform_celerity(const InstDev &I)
+{
+    if constexpr ((VK & VK_PLUS_ONE) != 0) return R(1);
+    else if constexpr ((VK & VK_MINUS_ONE) != 0) return R(-1);
+    else return R(I.v0);
+}
+
 template <typename R, typename S, int LK, int VK, bool FIELD, int MODE, bool HSUM = false>
 __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int lane, int half)
 {
@@ -883,7 +894,7 @@ __device__ __forceinline__ void run_tile(InstDev I, int strip, int chunk, int la
         constexpr int h = p & 1, hp = h ^ 1;              // this row's and the previous row's slope / Hhat
         const R ym1 = R(y[(p + 7) & 7]), y0 = R(y[p]), yp1 = R(y[(p + 1) & 7]);
         const R wx = R(wx_[c]);
-        const R v0 = FIELD ? R(v0_[c]) : R(I.v0);
+        const R v0 = FIELD ? R(v0_[c]) : uniform_celerity<VK, R>(I);
         const R b12 = R(b12_[c]), b11 = R(b11_[c]);
         // Operands of row k0+it+kAhead.  Issued on every iteration, so the
         // wait for this row's operands never has to drain loads just issued;
@@ -1204,7 +1215,7 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         y0 = R(y[p]);
         yp1 = R(y[(p + 1) & 7]);
         wx = R(wx_[p]);
-        v0 = FIELD ? R(v0_[p]) : R(I.v0);
+        v0 = FIELD ? R(v0_[p]) : uniform_celerity<VK, R>(I);
         b11_[(p + 3) & 3] = y[(p + 7) & 7];
         b12_[p & 3] = wx_[p];
         if constexpr (FIELD) vb_[p & 3] = v0_[p];
@@ -1264,7 +1275,7 @@ __device__ __forceinline__ void run_tile_fused(const InstDev &I, int strip, int 
         operands_a(it, phase, ym1a, y0a, yp1a, wxa, v0a);
         const R ym1b = R(wyo[p & 3]), y0b = R(wyo[(p + 1) & 3]), yp1b = R(wyo[(p + 2) & 3]);
         const R wxb = R(wxo[(p + 1) & 3]);
-        const R v0b = FIELD ? R(vb_[(p + 1) & 3]) : R(I.v0);
+        const R v0b = FIELD ? R(vb_[(p + 1) & 3]) : uniform_celerity<VK, R>(I);
         const R b12 = R(b12_[(p + 1) & 3]), b11 = R(b11_[p & 3]);   // the step's initial state
         if constexpr (kF64) {
             R q[4], hv;
@@ -1446,6 +1457,19 @@ hipError_t launch_fused_t(const InstDev &I, int dir, hipStream_t s)
     return hipGetLastError();
 }
 
+// The kernel kind of a float launch over one instance with a uniform celerity.
+// These launches are bound by VALU issue from about 1024^2 on; without the
+// products with the celerity a step takes (us, against the general kind):
+// 2048^2 minmod 23.4 / 24.7, superbee 25.5 / 26.9, 4096^2 70.3 / 74.7, Euler
+// steps 2048^2 11.7 / 12.1, fully discrete 2048^2 15.9 / 16.6, 4096^2 45.0 /
+// 47.5; smaller grids, bound by latency, 512^2 5.81 / 5.89.
+template <int VK, typename F> hipError_t with_uniform(const InstDev &I, F f)
+{
+    if (I.v0 == 1.0f) return f(std::integral_constant<int, VK | VK_PLUS_ONE>{});
+    if (I.v0 == -1.0f) return f(std::integral_constant<int, VK | VK_MINUS_ONE>{});
+    return f(std::integral_constant<int, VK>{});
+}
+
 template <typename R, typename S, int INTEG>
 hipError_t launch_fused_r(const InstDev &I, int dir, hipStream_t s)
 {
@@ -1456,11 +1480,19 @@ hipError_t launch_fused_r(const InstDev &I, int dir, hipStream_t s)
         if constexpr (kFD) {
             if (I.vkind == VK_PRESCRIBED_FD) return launch_fused_t<R, S, L, VK_PRESCRIBED_FD, false, INTEG>(I, dir, s);
             if (I.vkind == VK_LAW_FD && I.v0f) return launch_fused_t<R, S, L, VK_LAW_FD, true, INTEG>(I, dir, s);
-            if (I.vkind == VK_LAW_FD) return launch_fused_t<R, S, L, VK_LAW_FD, false, INTEG>(I, dir, s);
+            if (I.vkind == VK_LAW_FD)
+                return with_uniform<VK_LAW_FD>(I, [&](auto vk) {
+                    return launch_fused_t<R, S, L, decltype(vk)::value, false, INTEG>(I, dir, s);
+                });
         }
         if (I.vkind == VK_PRESCRIBED) return launch_fused_t<R, S, L, VK_PRESCRIBED, false, INTEG>(I, dir, s);
         if (I.v0f != nullptr) return launch_fused_t<R, S, L, VK_LAW, true, INTEG>(I, dir, s);
-        return launch_fused_t<R, S, L, VK_LAW, false, INTEG>(I, dir, s);
+        if constexpr (sizeof(R) == 4)
+            return with_uniform<VK_LAW>(I, [&](auto vk) {
+                return launch_fused_t<R, S, L, decltype(vk)::value, false, INTEG>(I, dir, s);
+            });
+        else
+            return launch_fused_t<R, S, L, VK_LAW, false, INTEG>(I, dir, s);
     });
 }
 
@@ -1478,7 +1510,12 @@ hipError_t launch_stage_r(const InstDev &I, int mode, hipStream_t s)
         case VK_LAW_FD:
             if (field && hsum) return launch_stage_t<R, S, L, VK_LAW_FD, true, true>(I, mode, s);
             if (field) return launch_stage_t<R, S, L, VK_LAW_FD, true>(I, mode, s);
-            return launch_stage_t<R, S, L, VK_LAW_FD, false>(I, mode, s);
+            if constexpr (sizeof(R) == 4)
+                return with_uniform<VK_LAW_FD>(I, [&](auto vk) {
+                    return launch_stage_t<R, S, L, decltype(vk)::value, false>(I, mode, s);
+                });
+            else
+                return launch_stage_t<R, S, L, VK_LAW_FD, false>(I, mode, s);
         default:
             if (field && hsum) return launch_stage_t<R, S, L, VK_LAW, true, true>(I, mode, s);
             if (field) return launch_stage_t<R, S, L, VK_LAW, true>(I, mode, s);

@@ -375,3 +375,26 @@ def test_two_single_stage_steps_a_launch_bitwise(fdm, nx, ny, kind, scheme):
         fdm.fdm_transport_step_noalloc(fdm.desc(nx, ny, **kw), t11, t12, 7)
         torch.cuda.synchronize()
         assert np.array_equal(t11.cpu().numpy(), p[6][1]) and np.array_equal(t12.cpu().numpy(), p[6][2])
+
+
+@pytest.mark.parametrize("v0", [1.0, -1.0])
+@pytest.mark.parametrize("order,scheme", [(1, "semidiscrete"), (2, "semidiscrete"), (3, "semidiscrete"),
+                                          (1, "fully_discrete")])
+@pytest.mark.parametrize("limiter", ["none", "minmod", "mc", "theta", "superbee"])
+def test_unit_celerity_bitwise(fdm, v0, order, scheme, limiter):
+    """One instance with the uniform celerity +1 or -1 has kernels without the
+    products with it: the bits of the same celerity given as a node field, for
+    pairs of steps and a single last one, with zeros and tiny densities in the
+    state."""
+    rng = np.random.default_rng(17)
+    for nx, ny in ((64, 31), (113, 9)):
+        a11, a12 = (rng.standard_normal((ny, nx)).astype(np.float32) for _ in range(2))
+        for a in (a11, a12):
+            a[rng.random(a.shape) < 0.3] = 0.0
+            a[rng.random(a.shape) < 0.2] *= np.float32(1e-25)
+        kw = dict(limiter=limiter, theta=1.4, cfl=0.25, time_order=order, scheme=scheme)
+        field = np.full((ny, nx), v0, np.float32)
+        for schedule in ("auto", "plain"):
+            _, u = gpu_run(a11, a12, 5, options={"schedule": schedule}, v0=v0, **dict(kw))
+            _, f = gpu_run(a11, a12, 5, options={"schedule": "plain"}, v0_field=field, **dict(kw))
+            assert np.array_equal(u[-1][1], f[-1][1]) and np.array_equal(u[-1][2], f[-1][2]), (nx, ny, schedule)
