@@ -143,7 +143,7 @@ bool fused_by_default(const fdm_transport_desc *descs, int32_t n, int32_t precis
     // with a field 64^2 1.9 / 2.6, 512^2 3.0 / 4.0, 2048^2 13.1 / 15.6, 4096^2
     // 42 / 71; fully discrete 64^2 2.1 / 2.7, 512^2 3.5 / 4.2, 1009 x 757 6.0 /
     // 6.3, but 2048^2 17.7 / 17.1 (its arithmetic, 1.2 times as much fused,
-    // bounds it there), 4096^2 61 / 60.
+    // bounds it there), 4096^2 61 / 60 (uniform celerities other than +-1).
     if (precision == FDM_PRECISION_FP32 && order == 1)
         return n == 1 && (!fd || (int64_t)d.nx * d.ny <= (int64_t)1 << 20);
     if (precision == FDM_PRECISION_FP32) return fused_applies(precision, order, fd);
@@ -171,8 +171,8 @@ int balanced_height(const std::function<int64_t(int)> &waves, int max_ny, int64_
 // results), and a tile of h rows costs h + 3 of them with its extra row and
 // its first loads.  So the height is the smallest that fits w waves per SIMD
 // for the w of 1 .. 8 with the least (h + 3)(1 + w).  Measured against
-// pick_rows (us a step): fully discrete 64^2 2.77 / 3.64, 300 x 200 2.81 /
-// 3.73, 512^2 4.28 / 4.49, 1009 x 757 6.29 / 6.86, 1536^2 12.2 / 13.0;
+// pick_rows (us a step, uniform celerity other than +-1): fully discrete 64^2
+// 2.77 / 3.64, 300 x 200 2.81 / 3.73, 512^2 4.28 / 4.49, 1009 x 757 6.29 / 6.86, 1536^2 12.2 / 13.0;
 // float64 state, both stages, 64^2 7.5 / 11.5, 512^2 14.1 / 16.9, 1009 x 757
 // 24.9 / 29.4, 1536^2 58.2 / 60.9.  Launches of more than 5 waves per SIMD at
 // pick_rows' height keep it, the evenness matters less there: 2048^2 fully
@@ -204,7 +204,8 @@ int stage_rows_of(const fdm_transport_desc &d, int64_t simds)
 
 // A launch that is resident at once takes the time of the SIMD with the most
 // waves, w, and a wave's time is linear in its height h.  Fitted over
-// 300 x 200 to 4096^2 and 1 to 75 rows (minmod, uniform celerity, us):
+// 300 x 200 to 4096^2 and 1 to 75 rows (minmod, uniform celerity other than
+// +-1, us; those take 5% less at 2048^2 and choose the same heights to 1%):
 //   3.4 + 0.75 w + (0.16 + 0.195 w) h,
 // the first part the launch, the loads and the first stage's extra rows, the
 // second the issue time of w waves (a lone wave also waits for its own
