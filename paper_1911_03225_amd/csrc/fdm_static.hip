@@ -325,7 +325,14 @@ __global__ __launch_bounds__(kLineThreads) void columns_kernel(T *__restrict__ s
                 const auto o = product(line >> 1, i == 0 ? 0 : ny - i);
                 return Cx<T>{o.tau.re + o.phi.im, o.phi.re - o.tau.im};
             },
-            [&](int line, int k, Cx<T> v) { cx_spec[place(line, k)] = v; }, [] {});
+            [&](int line, int k, Cx<T> v) {
+                // a pair that is one column (m1 = 0 or nx / 2) has one writer: its two
+                // lines are equal in exact arithmetic, not in bits
+                const int p = p0 + (line >> 1);
+                if ((line & 1) != 0 && (p == 0 || 2 * p == nx)) return;
+                cx_spec[place(line, k)] = v;
+            },
+            [] {});
     } else {
         fft_lines<true, false, POW2>(
             l.m, ay, np, [&](int q, int i) { return product(q, i).tau; },
