@@ -236,14 +236,18 @@ __global__ __launch_bounds__(kLineThreads) void rows_kernel(const T *__restrict_
 
 // Columns m1 and nx - m1 side by side (`pairs` of them a block): transform,
 // T = multiplier times the numerator (sigma_bar at the mean), transform back
-// into the column's place.  PHI: T + i P, P = phi^ / N with phi_mean at the
-// mean, into both columns (their transforms back give tau + i phi).
+// into the column's place.  PHI: T + i P, P = phi^ / N, into both columns
+// (their transforms back give tau + i phi).  A transform's rounding is that of
+// its larger part, and tau and phi share one here: so P is taken in units of
+// the power of two nearest below mu (phi_unit, which is exact; tau is of the
+// size of mu times phi at most), and the means stay out of it and are added to
+// the nodes.  With mu = 80e9 and P as it is, phi was off by 1e-5 of itself.
 template <typename T, bool PHI, bool POW2>
 __global__ __launch_bounds__(kLineThreads) void columns_kernel(T *__restrict__ spec, const T *__restrict__ K,
                                                                const T *__restrict__ d1, const T *__restrict__ d2,
                                                                const T *__restrict__ tw, int nx, int ny, int pairs,
-                                                               bool copy, FftAxis ay, T inv_n, const CoupledDev *cd,
-                                                               double sigma)
+                                                               bool copy, FftAxis ay, T unit_over_n,
+                                                               const CoupledDev *cd, double sigma)
 {
     const int nxh = nx / 2 + 1, p0 = (int)blockIdx.x * pairs, np = min(pairs, nxh - p0);
     LineLds<T> l(tw, copy, ny, 2 * pairs);
@@ -255,8 +259,8 @@ __global__ __launch_bounds__(kLineThreads) void columns_kernel(T *__restrict__ s
     const T *gmult = K + (int64_t)p0 * ny;
     Table<Cx<T>> sym_ahead;
     Table<T> mult_ahead;
-    // (early loads too: the mean stress and slip, and the pairs' symbols)
-    const T sigma_bar = (T)(cd ? cd->sigma_bar : sigma), phi_mean = (T)(PHI ? cd->phi_mean : 0.0);
+    // (early loads too: the mean stress, and the pairs' symbols)
+    const T mean_tau = PHI ? T(0) : (T)(cd ? cd->sigma_bar : sigma);
     Cx<T> sym1[kMaxPairs];
 #pragma unroll
     for (int q = 0; q < kMaxPairs; ++q) sym1[q] = reinterpret_cast<const Cx<T> *>(d1)[p0 + min(q, np - 1)];
@@ -306,10 +310,10 @@ __global__ __launch_bounds__(kLineThreads) void columns_kernel(T *__restrict__ s
         struct Out {
             Cx<T> tau, phi;
         } o{{f * nr, f * ni}, {T(0), T(0)}};
-        if (mean) o.tau = Cx<T>{sigma_bar, T(0)};
+        if (mean) o.tau = Cx<T>{mean_tau, T(0)};
         if constexpr (PHI) {
-            const T g = inv_n / ((d1r * d1r + d1i * d1i) + (d2r * d2r + d2i * d2i));
-            o.phi = mean ? Cx<T>{phi_mean, T(0)} : Cx<T>{g * nr, g * ni};
+            const T g = unit_over_n / ((d1r * d1r + d1i * d1i) + (d2r * d2r + d2i * d2i));
+            if (!mean) o.phi = Cx<T>{g * nr, g * ni};
         }
         return o;
     };
@@ -387,16 +391,19 @@ struct AbsMax {
 // LAW_NONE: tau13 to `tau`; otherwise the celerity to v0 and a partial of
 // its maximum per block.  Without phi the spectrum's rows are conjugate
 // symmetric and two of them make one complex line (row k in the real part,
-// row k + 1 in the imaginary one); with phi a line is tau + i phi.
+// row k + 1 in the imaginary one); with phi a line is tau + i phi, without
+// their means and phi in units of 1 / per_unit (see columns_kernel).
 enum : int { LAW_NONE = 0, LAW_SOFT = 1, LAW_WIGGLY = 2 };
 
 template <typename T, int LAW, bool POW2>
 __global__ __launch_bounds__(kLineThreads) void rows_back_kernel(const T *__restrict__ spec, T *__restrict__ tau,
                                                                  float *__restrict__ v0, const T *__restrict__ tw,
                                                                  int nx, int ny, int rows, int groups, bool copy,
-                                                                 FftAxis ax, LawArgs<T> L, float *__restrict__ partial)
+                                                                 FftAxis ax, LawArgs<T> L, const CoupledDev *cd,
+                                                                 T per_unit, float *__restrict__ partial)
 {
     constexpr bool PHI = LAW == LAW_WIGGLY;
+    const T sigma_bar = (T)(PHI ? cd->sigma_bar : 0.0), phi_mean = (T)(PHI ? cd->phi_mean : 0.0);
     const int lines = PHI ? rows : rows / 2;
     LineLds<T> l(tw, copy, nx, lines);
     const FftLds<T> m0 = l.m;
@@ -435,7 +442,7 @@ __global__ __launch_bounds__(kLineThreads) void rows_back_kernel(const T *__rest
             },
             [&](int r, int i, Cx<T> v) {
                 if constexpr (PHI) {
-                    leave(k0 + r, i, v.re, v.im);
+                    leave(k0 + r, i, v.re + sigma_bar, v.im * per_unit + phi_mean);
                 } else {
                     leave(k0 + 2 * r, i, v.re, T(0));
                     leave(k0 + 2 * r + 1, i, v.im, T(0));
@@ -808,11 +815,13 @@ StaticStatus run_own(StaticPlan *p, const void *a11, const void *a12, const Solv
     ST_HIP(hipGetLastError());
     const bool wiggly = out.law && out.law->wiggly;
     const dim3 cols((unsigned)((p->nxh + p->shape.pairs - 1) / p->shape.pairs));
-    const T inv_n = (T)(1.0 / ((double)nx * (double)ny));
+    // (an exponent that keeps 2^e and 2^-e finite)
+    const int e = wiggly ? std::max(-1000, std::min(1000, std::ilogb(p->mu))) : 0;
+    const T unit_over_n = (T)std::ldexp(1.0 / ((double)nx * (double)ny), e), per_unit = (T)std::ldexp(1.0, -e);
     auto columns = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, cols, threads, p->shape.lds_cols, s, spec, (const T *)p->K, (const T *)p->d1,
                            (const T *)p->d2, (const T *)p->twy, nx, ny, p->shape.pairs, p->shape.copy_cols, p->ay,
-                           inv_n, cd, sigma);
+                           unit_over_n, cd, sigma);
     };
     if (wiggly && py) columns(columns_kernel<T, true, true>);
     else if (wiggly) columns(columns_kernel<T, true, false>);
@@ -822,7 +831,7 @@ StaticStatus run_own(StaticPlan *p, const void *a11, const void *a12, const Solv
     auto back = [&](auto kernel, const LawArgs<T> &L) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(groups, kLawBlocks)), threads, p->shape.lds_rows, s,
                            (const T *)spec, (T *)out.tau, out.v0, (const T *)p->twx, nx, ny, p->shape.rows, groups,
-                           p->shape.copy_rows, p->ax, L, out.partial);
+                           p->shape.copy_rows, p->ax, L, cd, per_unit, out.partial);
     };
     const LawArgs<T> L = out.law ? law_args<T>(*out.law) : LawArgs<T>{};
     if (!out.law && px) back(rows_back_kernel<T, LAW_NONE, true>, L);

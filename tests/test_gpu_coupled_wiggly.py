@@ -60,3 +60,33 @@ def test_two_runs_give_the_same_bits_and_follow_the_oracle(fdm, nx, ny):
             assert g[k] == pytest.approx(o[k], rel=1e-10, abs=1e-13), (k, g[k], o[k])
     den = np.abs(a11).sum() + np.abs(a12).sum()
     assert (np.abs(g11 - o11).sum() + np.abs(g12 - o12).sum()) / den < 1e-10
+
+
+@pytest.mark.parametrize("power", [30, -30])
+def test_units_of_stress_do_not_matter(fdm, power):
+    """The same problem with every stress times a power of two and the
+    mobility divided by it takes the same steps bit for bit: phi does not
+    lose digits to a stress of another magnitude, nor the stress to phi."""
+    nx, ny = 96, 80
+    phi, a11, a12 = W.plateau_rings(nx, ny, seed=5, count=4, rmin=6.0, rmax=14.0)
+    mean, s = float(phi.mean()), 2.0 ** power
+    hist, g11, g12 = run(fdm, a11, a12, 24, 12, mean)
+    h, r11, r12 = run(fdm, a11, a12, 24, 12, mean, mu=LOAD["mu"] * s, lam=LOAD["lam"] * s, tau_y=LOAD["tau_y"] * s,
+                      mobility=LOAD["mobility"] / s)
+    assert np.array_equal(g11, r11) and np.array_equal(g12, r12)
+    for k in ("t", "dt", "eps13", "phi_mean", "vmax"):
+        assert h[-1][k] == hist[-1][k], k
+    assert h[-1]["sigma13"] == hist[-1]["sigma13"] * s
+
+
+def test_stresses_in_pascals_follow_the_oracle(fdm):
+    nx, ny = 75, 48
+    phi, a11, a12 = W.plateau_rings(nx, ny, seed=5, count=4, rmin=6.0, rmax=14.0)
+    load = dict(LOAD, mu=80e9, lam=120e9, tau_y=0.8e9, mobility=1.0 / 80e9)
+    hist, g11, g12 = run(fdm, a11, a12, 24, 12, float(phi.mean()), **load)
+    o11, o12, ohist = CP.coupled_run(a11, a12, 24, 12, cfl=0.4, dx=1.0, phi_mean=float(phi.mean()), **load)
+    for g, o in zip(hist, ohist):
+        for k in ("t", "eps13", "phi_mean", "sigma13"):
+            assert g[k] == pytest.approx(o[k], rel=1e-10), (k, g[k], o[k])
+    den = np.abs(a11).sum() + np.abs(a12).sum()
+    assert (np.abs(g11 - o11).sum() + np.abs(g12 - o12).sum()) / den < 1e-10
