@@ -68,6 +68,7 @@ struct fdm_ctx {
         fdm::CoupledDev *h_cd = nullptr;    // pinned mirror
         double eps13 = 0.0, sigma13 = 0.0, phi_mean = 0.0, vmax = 0.0;
         bool no_graph = false;              // a chunk could not be captured as kernels only
+        int64_t replays = 0;                // graph launches of all coupled runs
     } cw;
     size_t elem = sizeof(float);            // bytes per state value
     int64_t tile_capacity = 0;              // entries of d_tile_inst
@@ -454,6 +455,9 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
         w.q = q;
     }
     const fdm::LawParams law{wiggly, L.tau0, L.mobility, L.tau_y, L.beta, L.mobility_field};
+    // ahead of the capture below, which must not allocate
+    const fdm::StaticStatus prepared = fdm::static_plan_prepare(w.plan, law, err);
+    if (prepared != fdm::StaticStatus::Ok) return static_fail(c, prepared, err);
     if (!w.v0) FDM_HIP(c, hipMalloc((void **)&w.v0, sizeof(float) * n));
     InstDev I = c->inst[0];
     if (c->requested_rows <= 0) {
@@ -599,7 +603,8 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
             if (st != FDM_OK) return st;
             --left;
         }
-        for (; gexec && left >= kGraphSteps; left -= kGraphSteps) FDM_HIP(c, hipGraphLaunch(gexec, c->stream));
+        for (; gexec && left >= kGraphSteps; left -= kGraphSteps, ++w.replays)
+            FDM_HIP(c, hipGraphLaunch(gexec, c->stream));
         if (left > 0) {
             st = enqueue_chunk(left, done == 0 && !gexec, c->stream);
             if (st != FDM_OK) return st;
@@ -1061,6 +1066,10 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
     if (n_trials) *n_trials = std::min(count, max_trials);
     return st;
 }
+
+// Graph launches of the context's coupled runs so far.  For the tests alone:
+// not part of the interface, and not declared in fdm.h.
+int64_t fdm_test_coupled_replays(const fdm_ctx *c) { return c ? c->cw.replays : -1; }
 
 double fdm_transport_dt(const fdm_ctx *c, int32_t i)
 {

@@ -42,6 +42,10 @@ struct LawParams {
     const float *mfield;
 };
 
+// Allocates what static_plan_celerity needs with this law (kept with the
+// plan), so that it only launches kernels and its steps can be captured.
+StaticStatus static_plan_prepare(StaticPlan *p, const LawParams &law, std::string &err);
+
 // Where a coupled step's solve reads its densities from, if not from the
 // state itself: then the step's last stage also writes there, and
 // static_plan_celerity is called with null densities (the first step of a
@@ -53,7 +57,7 @@ bool static_plan_input(StaticPlan *p, void **a11, void **a12);
 // for the wiggly law, and the law.  slip (may be null): the previous step's
 // pending slip update, run ahead of everything that reads the mean stress or
 // slip.  Also writes static_plan_partials(p) partials of max |v0| (NaN marks
-// a non-finite value) for the step size.
+// a non-finite value) for the step size.  static_plan_prepare comes first.
 StaticStatus static_plan_celerity(StaticPlan *p, const void *a11, const void *a12, const LawParams &law,
                                   const CoupledDev *cd, const SlipArgs *slip, float *v0, float *partial,
                                   hipStream_t s, std::string &err);

@@ -854,12 +854,7 @@ StaticStatus run_rocfft(StaticPlan *p, const void *a11, const void *a12, const S
     if (slip) sa = *slip;
     const int64_t n = (int64_t)p->nx * p->ny, nm = (int64_t)p->nxh * p->ny;
     const bool wiggly = out.law && out.law->wiggly;
-    void *tau = out.tau;
-    if (out.law) {   // the first coupled step's buffers, kept with the plan
-        if (!p->tau) ST_HIP(hipMalloc(&p->tau, sizeof(T) * n));
-        if (wiggly && !p->phi) ST_HIP(hipMalloc(&p->phi, sizeof(T) * n));
-        tau = p->tau;
-    }
+    void *const tau = out.law ? p->tau : out.tau;
     ST_FFT(rocfft_execution_info_set_stream(p->info, s));
     const unsigned gb = (unsigned)((nm + 255) / 256);
     if (a11) {   // else the densities are in place already
@@ -913,6 +908,15 @@ static_assert(kLawBlocks <= kMaxPartials, "the stage kernels reduce at most kMax
 int static_plan_partials(const StaticPlan *p)
 {
     return p->own ? std::min(row_groups(p), kLawBlocks) : law_blocks((int64_t)p->nx * p->ny);
+}
+
+StaticStatus static_plan_prepare(StaticPlan *p, const LawParams &law, std::string &err)
+{
+    if (p->own) return StaticStatus::Ok;
+    const size_t bytes = (p->f64 ? sizeof(double) : sizeof(float)) * (size_t)p->nx * (size_t)p->ny;
+    if (!p->tau) ST_HIP(hipMalloc(&p->tau, bytes));
+    if (law.wiggly && !p->phi) ST_HIP(hipMalloc(&p->phi, bytes));
+    return StaticStatus::Ok;
 }
 
 bool static_plan_input(StaticPlan *p, void **a11, void **a12)

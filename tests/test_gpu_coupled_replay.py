@@ -1,0 +1,52 @@
+"""Coupled runs long enough to replay a captured graph of steps."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from gpu_util import to_dev
+from paper_1911_03225_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+LOAD = dict(strain_rate13=2e-3, tau0=0.005, mobility=1.0, mu=1.0, lam=1.5, layer_h=3.0, cell_l3=24.0,
+            dt_max=0.25, eps13=0.02, tau_y=0.01, beta=1e-2)
+
+
+@pytest.fixture(scope="module")
+def fdm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1911_03225_amd import fdm as F
+    F.load_library()
+    return F
+
+
+def _case(nx=72, ny=56):
+    phi, a11, a12 = W.plateau_rings(nx, ny, seed=5, count=4, rmin=6.0, rmax=14.0)
+    return float(phi.mean()), a11, a12
+
+
+def _replays(fdm, ctx):
+    f = fdm.load_library().fdm_test_coupled_replays   # (the library's counter for this test)
+    f.argtypes, f.restype = [ctypes.c_void_p], ctypes.c_int64
+    return f(ctx.handle)
+
+
+@pytest.mark.parametrize("precision,laws", [("fp32", ["threshold"]), ("fp32", ["wiggly"]),
+                                            ("fp32", ["threshold", "wiggly"]), ("fp64", ["threshold"]),
+                                            ("fp64", ["wiggly"])])
+def test_a_fresh_context_replays(fdm, precision, laws):
+    """The first call of 200 steps replays graphs, with either law and with
+    the other law's run before it: nothing is allocated while capturing."""
+    mean, a11, a12 = _case()
+    dt = np.float64 if precision == "fp64" else np.float32
+    t11, t12 = to_dev(a11, dt), to_dev(a12, dt)
+    ctx = fdm.fdm_transport_init(fdm.desc(72, 56, cfl=0.4, v0=-1.0), options={"precision": precision})
+    for law in laws:
+        before = _replays(fdm, ctx)
+        fdm.fdm_run(ctx, t11, t12, 200, 200, loading=fdm.loading(phi_mean=mean, law=law, **LOAD))
+        n = _replays(fdm, ctx) - before
+        assert n >= 12, (law, n)   # sixteen steps a graph
+    fdm.fdm_destroy(ctx)
