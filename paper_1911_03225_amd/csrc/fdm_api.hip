@@ -517,7 +517,8 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
     // it reads them (later steps' last stage leaves them there: 3 us a step
     // at 512^2 for the kernel that did).
     void *in11 = nullptr, *in12 = nullptr;
-    const bool twice = fdm::static_plan_input(w.plan, &in11, &in12) && stages == 2;
+    const bool library_fft = fdm::static_plan_input(w.plan, &in11, &in12);
+    const bool twice = library_fft && stages == 2;
     auto enqueue_chunk = [&](int32_t m, bool first, hipStream_t s) -> fdm_status {
         InstDev J = I;
         for (int32_t j = 0; j < m; ++j) {
@@ -545,24 +546,41 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
         return FDM_OK;
     };
 
-    // Runs of steps replay one captured graph of kGraphSteps of them (kernel
+    // Runs of steps replay one captured graph of graph_steps of them (kernel
     // nodes only; a capture that fails or records anything else leaves the
-    // steps enqueued one kernel at a time, with the same kernels).  A replayed
-    // step saves the host's launches (up to 7 us a step on small grids, 2 at
-    // 512^2), but capturing and instantiating costs 35 to 50 us for each step
-    // of the graph, 5 ms for a chunk of 100 that a run of 400 does not earn
-    // back (58 us a step against 45), so the graph is short and calls too short
-    // for it go without.
-    constexpr int32_t kGraphSteps = 16, kGraphLeast = 160;
+    // steps enqueued one kernel at a time, with the same kernels): at most 16,
+    // an equal share of a chunk, so that at most a few are left over.  A
+    // replayed step saves the host's launches, capturing and instantiating
+    // costs 35 to 50 us for each step of the graph (a graph of 64 steps instead
+    // of 16 makes a run of 200 1.1 times as long).  What that saves is small
+    // where the host is well ahead of the GPU; but each chunk ends with a wait,
+    // after which it is not.  Measured, us a step with replays / without, the
+    // capture included:
+    //   float, chunks of 8, 200 steps: 64^2 30.2 / 34.9, 512^2 43.5 / 48.4,
+    //     1024^2 89.5 / 95.9, 2048^2 237 / 236; chunks of 1: 300 x 200 80.0 / 84.1;
+    //     five chunks of 8 or of 20, from a host whose launches are slow: 96 x 80
+    //     34.3 / 42.4 and 39.1 / 49.1, 1024^2 95.7 / 88.9 and 89.2 / 86.5;
+    //   double (own transforms, half the launches), 512^2, chunks of 8 56.0 /
+    //     56.4, of 4 60.2 / 60.3, of 1 85 / 83;
+    //   one chunk: 64^2, 200 steps 27.6 / 27.5 (29 to 32 / 33 to 37 from a host
+    //     whose launches are slow); 512^2, 200 steps 41.7 / 40.8, 400 40.1 / 40.7,
+    //     1600 39.1 / 40.5; 1024^2, 800 steps 85.6 / 84.3.
+    constexpr int32_t kGraphMost = 16;
+    const int32_t run = std::min(chunk, n_steps);
+    const int32_t graph_steps = run / std::max(1, (int32_t)(((int64_t)run + kGraphMost - 1) / kGraphMost));
+    const bool waits = chunk < 64;
+    const bool small = n < (int64_t)1 << 17, large = n >= (int64_t)1 << 20;
+    const int64_t graph_least = waits && library_fft && !large ? 5 * graph_steps : waits || small ? 160 : 400;
+    const bool worth = n_steps >= graph_least && (waits ? chunk >= (library_fft ? 1 : 4) : !large);
     hipGraphExec_t gexec = nullptr;
-    if (n_steps >= kGraphLeast && chunk >= kGraphSteps && !w.no_graph) {
+    if (worth && !w.no_graph) {
         FDM_HIP(c, hipStreamSynchronize(c->stream));
         const bool sticky0 = c->sticky;
         const std::string err0 = c->err;
         hipGraph_t g = nullptr;
         bool ok = hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal) == hipSuccess;
         if (ok) {
-            const fdm_status cs = enqueue_chunk(kGraphSteps, false, c->capture);
+            const fdm_status cs = enqueue_chunk(graph_steps, false, c->capture);
             ok = hipStreamEndCapture(c->capture, &g) == hipSuccess && cs == FDM_OK && g != nullptr;
         }
         size_t nn = 0;
@@ -603,7 +621,7 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
             if (st != FDM_OK) return st;
             --left;
         }
-        for (; gexec && left >= kGraphSteps; left -= kGraphSteps, ++w.replays)
+        for (; gexec && left >= graph_steps; left -= graph_steps, ++w.replays)
             FDM_HIP(c, hipGraphLaunch(gexec, c->stream));
         if (left > 0) {
             st = enqueue_chunk(left, done == 0 && !gexec, c->stream);

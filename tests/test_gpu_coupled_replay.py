@@ -48,5 +48,19 @@ def test_a_fresh_context_replays(fdm, precision, laws):
         before = _replays(fdm, ctx)
         fdm.fdm_run(ctx, t11, t12, 200, 200, loading=fdm.loading(phi_mean=mean, law=law, **LOAD))
         n = _replays(fdm, ctx) - before
-        assert n >= 12, (law, n)   # sixteen steps a graph
+        assert n >= 12, (law, n)
     fdm.fdm_destroy(ctx)
+
+
+@pytest.mark.parametrize("chunk,least", [(1, 199), (4, 49), (8, 24), (15, 12), (20, 19)])
+def test_short_chunks_replay(fdm, chunk, least):
+    """A chunk below sixteen steps is one replay, a longer one whole shares of
+    it: of 200 steps none but the first chunk's and a short last one's, and a
+    step or two a chunk, are enqueued kernel by kernel."""
+    mean, a11, a12 = _case()
+    t11, t12 = to_dev(a11, np.float32), to_dev(a12, np.float32)
+    ctx = fdm.fdm_transport_init(fdm.desc(72, 56, cfl=0.4, v0=-1.0))
+    fdm.fdm_run(ctx, t11, t12, 200, chunk, loading=fdm.loading(phi_mean=mean, **LOAD))
+    n = _replays(fdm, ctx)
+    fdm.fdm_destroy(ctx)
+    assert n >= least, n
