@@ -64,3 +64,40 @@ def test_short_chunks_replay(fdm, chunk, least):
     n = _replays(fdm, ctx)
     fdm.fdm_destroy(ctx)
     assert n >= least, n
+
+
+@pytest.mark.parametrize("precision,law,time_order", [("fp32", "threshold", 2), ("fp32", "wiggly", 2),
+                                                      ("fp32", "threshold", 1), ("fp64", "threshold", 3),
+                                                      ("fp64", "wiggly", 2)])
+def test_replayed_steps_give_the_bits_of_direct_ones(fdm, precision, law, time_order):
+    """200 steps in twenty calls too short to replay anything, against one
+    call, and two calls of the same context, in chunks that are whole shares
+    of a graph, that leave steps over, and that wait after every step: the
+    same state and scalars bit for bit, with the diagnostics of every chunk
+    read between the replays."""
+    mean, a11, a12 = _case()
+    cfl = 0.25 if time_order == 1 else 0.4
+    dt = np.float64 if precision == "fp64" else np.float32
+
+    def run(calls, n, chunk):
+        t11, t12 = to_dev(a11, dt), to_dev(a12, dt)
+        ctx = fdm.fdm_transport_init(fdm.desc(72, 56, cfl=cfl, v0=-1.0, time_order=time_order),
+                                     options={"precision": precision})
+        h = dict(phi_mean=mean, eps13=LOAD["eps13"])
+        for _ in range(calls):
+            load = dict(LOAD, law=law, phi_mean=h["phi_mean"], eps13=h["eps13"])
+            h = fdm.fdm_run(ctx, t11, t12, n, chunk, loading=fdm.loading(**load))[-1][0]
+        r = _replays(fdm, ctx)
+        fdm.fdm_destroy(ctx)
+        return h, t11.cpu().numpy(), t12.cpu().numpy(), r
+
+    ref, r11, r12, replays = run(20, 10, 10)
+    assert replays == 0 and ref["step"] == 200
+    for calls, n, chunk in ((1, 200, 200), (1, 200, 40), (1, 200, 17), (1, 200, 16), (1, 200, 7), (1, 200, 1),
+                            (2, 100, 25)):
+        h, g11, g12, replays = run(calls, n, chunk)
+        # (float64 runs replay from 160 steps and chunks of four on)
+        assert (replays > 0) == (precision == "fp32" or (n >= 160 and chunk >= 4)), (chunk, replays)
+        assert np.array_equal(g11, r11) and np.array_equal(g12, r12), (calls, chunk)
+        for k in ("step", "t", "dt", "eps13", "sigma13", "phi_mean", "vmax", "sum_abs"):
+            assert h[k] == ref[k], (calls, chunk, k, h[k], ref[k])
