@@ -177,10 +177,10 @@ __global__ __launch_bounds__(kStatsBlocks) void stats_final_kernel(const StatsPa
                                                                    double *__restrict__ out)
 {
     __shared__ StatsPartial lds[kStatsBlocks / 64];
-    int first = 0;
+    int64_t first = 0;
     if (insts) {
         const InstDev &I = insts[blockIdx.x];
-        first = (int)I.stats_first;
+        first = I.stats_first;
         blocks = stats_blocks((int64_t)I.nx * I.ny);
     }
     StatsPartial p{0, 0, 0, 0, 0, 0, 0, 0};
@@ -300,14 +300,21 @@ hipError_t launch_stats(const void *a11, const void *a12, int64_t n, int precisi
 hipError_t launch_stats_batched(const InstDev *d_inst, int n_inst, int most_blocks, int precision,
                                 StatsPartial *d_partials, double *out, hipStream_t s)
 {
-    const dim3 grid(most_blocks, n_inst);
-    if (precision == PREC_FP64)
-        hipLaunchKernelGGL(stats_batched_kernel<double>, grid, dim3(256), 0, s, d_inst, d_partials);
-    else
-        hipLaunchKernelGGL(stats_batched_kernel<float>, grid, dim3(256), 0, s, d_inst, d_partials);
-    hipLaunchKernelGGL(stats_final_kernel, dim3(n_inst), dim3(kStatsBlocks), 0, s, (const StatsPartial *)d_partials, 0,
-                       d_inst, out);
-    return hipGetLastError();
+    constexpr int kMostRows = 32768;   // instances a launch: a device takes 65536 blocks along y
+    for (int at = 0; at < n_inst; at += kMostRows) {
+        const int rows = n_inst - at < kMostRows ? n_inst - at : kMostRows;
+        const InstDev *insts = d_inst + at;
+        const dim3 grid(most_blocks, rows);
+        if (precision == PREC_FP64)
+            hipLaunchKernelGGL(stats_batched_kernel<double>, grid, dim3(256), 0, s, insts, d_partials);
+        else
+            hipLaunchKernelGGL(stats_batched_kernel<float>, grid, dim3(256), 0, s, insts, d_partials);
+        hipLaunchKernelGGL(stats_final_kernel, dim3(rows), dim3(kStatsBlocks), 0, s, (const StatsPartial *)d_partials,
+                           0, insts, out + 5 * (int64_t)at);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_copy(void *dst, const void *src, int64_t n, int precision, hipStream_t s)
