@@ -220,16 +220,15 @@ struct StatsPartial {
     double s11, c11, s12, c12, sab, cab, maxn, nonfinite;
 };
 
-// Blocks that sum an instance's diagnostics, by its size alone (so the
-// reduction order is deterministic): one block of 1024 threads does up to
-// 16384 nodes (one launch, no partials: 64^2 5.5 us against 5.7 + 5.3 for 512
-// blocks and their fold), beyond that 2048 nodes a block of 256 threads, at
-// most 512 blocks.
-constexpr int kStatsBlocks = 512;
-constexpr int kStatsSmallThreads = 1024;
+// Blocks of kStatsThreads threads that sum an instance's diagnostics, by its
+// size alone (so the order of the sums is, whatever the schedule): one does up
+// to 8192 nodes (one launch, no partials: a call at 128 x 64 17.4 us, at 64^2
+// 15.6; five blocks and their fold, at 100^2, 19.5), beyond that 2048 nodes a
+// block, at most 512 blocks (4096^2 49 us a call).
+constexpr int kStatsBlocks = 512, kStatsThreads = 256;
 __host__ __device__ inline int stats_blocks(int64_t nodes)
 {
-    if (nodes <= 16 * kStatsSmallThreads) return 1;
+    if (nodes <= 8192) return 1;
     const int64_t b = (nodes + 2047) / 2048;
     return b < kStatsBlocks ? (int)b : kStatsBlocks;
 }

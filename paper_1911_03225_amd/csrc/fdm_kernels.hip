@@ -99,25 +99,47 @@ __device__ __forceinline__ void neumaier(double &s, double &c, double x)
 }
 
 // The diagnostics of one pair of arrays by the blocks 0 .. blocks-1 of a
-// launch; the largest norm is kept as its square (the root of the largest is
-// the largest root, correctly rounded either way).
+// launch, each of kStatsThreads threads whatever the kernel, so the order of
+// the sums follows from the number of nodes alone; the largest norm is kept as
+// its square (the root of the largest is the largest root, correctly rounded
+// either way).  A thread's next kAhead values load together, then add in order.
 template <typename S>
 __device__ __forceinline__ void stats_sum(const S *__restrict__ a11, const S *__restrict__ a12, int64_t n, int block,
                                           int blocks, StatsPartial *lds, StatsPartial &p)
 {
     p = StatsPartial{0, 0, 0, 0, 0, 0, 0, 0};
-    const int64_t stride = (int64_t)blocks * blockDim.x;
-    for (int64_t i = (int64_t)block * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const S x = a11[i], y = a12[i];
-        if (!isfinite(x) || !isfinite(y)) {
-            p.nonfinite += 1.0;
-            continue;
-        }
-        const double dx = x, dy = y;
+    constexpr int kAhead = 4;
+    const int64_t stride = (int64_t)blocks * kStatsThreads;
+    auto add = [&](S x, S y, bool in) {   // (a value left out adds 0, which changes no bit)
+        const bool finite = isfinite(x) && isfinite(y);
+        const double dx = in && finite ? (double)x : 0.0, dy = in && finite ? (double)y : 0.0;
+        p.nonfinite += in && !finite ? 1.0 : 0.0;
         neumaier(p.s11, p.c11, dx);
         neumaier(p.s12, p.c12, dy);
         neumaier(p.sab, p.cab, fabs(dx) + fabs(dy));
         p.maxn = fmax(p.maxn, dx * dx + dy * dy);
+    };
+    int64_t i = (int64_t)block * kStatsThreads + threadIdx.x;
+    for (; i + (kAhead - 1) * stride < n; i += kAhead * stride) {
+        S x[kAhead], y[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            x[u] = a11[i + u * stride];
+            y[u] = a12[i + u * stride];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) add(x[u], y[u], true);
+    }
+    if (i < n) {
+        S x[kAhead], y[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t at = i + u * stride < n ? i + u * stride : i;
+            x[u] = a11[at];
+            y[u] = a12[at];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) add(x[u], y[u], i + u * stride < n);
     }
     block_reduce(p, lds);
 }
@@ -133,21 +155,22 @@ __device__ __forceinline__ void stats_out(const StatsPartial &p, double *out)
 
 // One block does a small grid alone and writes the five results itself.
 template <typename S>
-__global__ __launch_bounds__(kStatsSmallThreads) void stats_small_kernel(const S *__restrict__ a11,
-                                                                         const S *__restrict__ a12, int64_t n,
-                                                                         double *__restrict__ out)
+__global__ __launch_bounds__(kStatsThreads) void stats_small_kernel(const S *__restrict__ a11,
+                                                                    const S *__restrict__ a12, int64_t n,
+                                                                    double *__restrict__ out)
 {
-    __shared__ StatsPartial lds[kStatsSmallThreads / 64];
+    __shared__ StatsPartial lds[kStatsThreads / 64];
     StatsPartial p;
     stats_sum<S>(a11, a12, n, 0, 1, lds, p);
     if (threadIdx.x == 0) stats_out(p, out);
 }
 
 template <typename S>
-__global__ __launch_bounds__(256) void stats_partial_kernel(const S *__restrict__ a11, const S *__restrict__ a12,
-                                                            int64_t n, StatsPartial *__restrict__ out)
+__global__ __launch_bounds__(kStatsThreads) void stats_partial_kernel(const S *__restrict__ a11,
+                                                                      const S *__restrict__ a12, int64_t n,
+                                                                      StatsPartial *__restrict__ out)
 {
-    __shared__ StatsPartial lds[4];
+    __shared__ StatsPartial lds[kStatsThreads / 64];
     StatsPartial p;
     stats_sum<S>(a11, a12, n, blockIdx.x, gridDim.x, lds, p);
     if (threadIdx.x == 0) out[blockIdx.x] = p;
@@ -156,10 +179,10 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(const S *__restrict_
 // Every instance of a batch in one launch: row y of the grid is instance y,
 // whose first stats_blocks(nodes) blocks sum it.
 template <typename S>
-__global__ __launch_bounds__(256) void stats_batched_kernel(const InstDev *__restrict__ insts,
-                                                            StatsPartial *__restrict__ out)
+__global__ __launch_bounds__(kStatsThreads) void stats_batched_kernel(const InstDev *__restrict__ insts,
+                                                                      StatsPartial *__restrict__ out)
 {
-    __shared__ StatsPartial lds[4];
+    __shared__ StatsPartial lds[kStatsThreads / 64];
     const InstDev &I = insts[blockIdx.y];
     const int64_t n = (int64_t)I.nx * I.ny;
     const int blocks = stats_blocks(n);
@@ -281,10 +304,10 @@ static void stats_launches(const void *a11, const void *a12, int64_t n, StatsPar
     const S *x = static_cast<const S *>(a11), *y = static_cast<const S *>(a12);
     const int blocks = stats_blocks(n);
     if (blocks == 1) {
-        hipLaunchKernelGGL(stats_small_kernel<S>, dim3(1), dim3(kStatsSmallThreads), 0, s, x, y, n, out);
+        hipLaunchKernelGGL(stats_small_kernel<S>, dim3(1), dim3(kStatsThreads), 0, s, x, y, n, out);
         return;
     }
-    hipLaunchKernelGGL(stats_partial_kernel<S>, dim3(blocks), dim3(256), 0, s, x, y, n, parts);
+    hipLaunchKernelGGL(stats_partial_kernel<S>, dim3(blocks), dim3(kStatsThreads), 0, s, x, y, n, parts);
     hipLaunchKernelGGL(stats_final_kernel, dim3(1), dim3(kStatsBlocks), 0, s, (const StatsPartial *)parts, blocks,
                        (const InstDev *)nullptr, out);
 }
@@ -306,9 +329,9 @@ hipError_t launch_stats_batched(const InstDev *d_inst, int n_inst, int most_bloc
         const InstDev *insts = d_inst + at;
         const dim3 grid(most_blocks, rows);
         if (precision == PREC_FP64)
-            hipLaunchKernelGGL(stats_batched_kernel<double>, grid, dim3(256), 0, s, insts, d_partials);
+            hipLaunchKernelGGL(stats_batched_kernel<double>, grid, dim3(kStatsThreads), 0, s, insts, d_partials);
         else
-            hipLaunchKernelGGL(stats_batched_kernel<float>, grid, dim3(256), 0, s, insts, d_partials);
+            hipLaunchKernelGGL(stats_batched_kernel<float>, grid, dim3(kStatsThreads), 0, s, insts, d_partials);
         hipLaunchKernelGGL(stats_final_kernel, dim3(rows), dim3(kStatsBlocks), 0, s, (const StatsPartial *)d_partials,
                            0, insts, out + 5 * (int64_t)at);
         const hipError_t e = hipGetLastError();

@@ -31,3 +31,39 @@ def test_more_instances_than_a_grid_dimension_holds(fdm):
     # six float values: their sums in double are exact to a few units of 2^-53 of 6
     assert np.allclose([s["sum11"] for s in got], s11, rtol=0, atol=1e-14)
     assert np.allclose([s["sum12"] for s in got], s12, rtol=0, atol=1e-14)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_the_sums_do_not_depend_on_the_schedule(fdm, precision):
+    """Sizes on both sides of one block, of a few and of all 512: a batch's
+    diagnostics are those of each instance by itself, bit for bit, also with
+    one instance a launch and with a large instance beside small ones."""
+    import torch
+    sizes = [(1, 1), (7, 5), (64, 64), (90, 91), (128, 64), (91, 91), (128, 128), (129, 128), (300, 200), (1100, 1000)]
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(2)
+    def values(nx, ny):   # of many magnitudes, and in pairs of both signs: what is left shows the order
+        u = torch.rand(ny, nx, device="cuda", dtype=torch.float64, generator=g)
+        x = torch.randn(ny, nx, device="cuda", dtype=torch.float64, generator=g) * 10.0 ** (30.0 * u - 15.0)
+        return (x - x.roll(1, 1)).to(dt)
+    t11 = [values(nx, ny) for nx, ny in sizes]
+    t12 = [values(nx, ny) for nx, ny in sizes]
+    keys = ("sum11", "sum12", "sum_abs", "max_norm", "nonfinite")
+    runs = []
+    for schedule in ("batched", "auto", "plain"):
+        ctx = fdm.fdm_transport_init([fdm.desc(nx, ny) for nx, ny in sizes],
+                                     options={"precision": precision, "schedule": schedule})
+        runs.append([[s[k] for k in keys] for s in fdm.fdm_transport_stats(ctx, t11, t12)])
+        fdm.fdm_destroy(ctx)
+    single = []
+    for (nx, ny), a, b in zip(sizes, t11, t12):
+        ctx = fdm.fdm_transport_init(fdm.desc(nx, ny), options={"precision": precision})
+        single.append([fdm.fdm_transport_stats(ctx, a, b)[0][k] for k in keys])
+        fdm.fdm_destroy(ctx)
+    for r in runs:
+        for size, x, y in zip(sizes, r, single):
+            assert x == y, (size, x, y)
+    for (nx, ny), x, a in zip(sizes, single, t11):
+        d = a.double()
+        # compensated sums: a few units in the last place of the sum of the values' sizes
+        assert abs(x[0] - float(d.sum().cpu())) <= 1e-13 * float(d.abs().sum().cpu()), (nx, ny)
