@@ -350,7 +350,13 @@ void advance(fdm_ctx *c, int32_t n)
 // Enqueues the diagnostics of the given arrays into h_stats.
 fdm_status enqueue_stats(fdm_ctx *c, void *const *a11, void *const *a12)
 {
-    if (c->batched) {   // one launch over the table of instances, and one that folds
+    // A batch: one launch over the table of instances, and one that folds, if
+    // the table is of these arrays (or still free).  Other arrays go instance
+    // by instance: steps that a caller has captured read the table.
+    bool here = c->batched;
+    for (int i = 0; here && c->table_valid && i < c->n; ++i)
+        here = c->inst[i].a11 == a11[i] && c->inst[i].a12 == a12[i];
+    if (here) {
         const fdm_status st = bind(c, a11, a12);
         if (st != FDM_OK) return st;
         FDM_HIP(c, fdm::launch_stats_batched(c->d_inst, c->n, c->stats_most, c->precision, c->d_partials, c->h_stats,

@@ -67,3 +67,41 @@ def test_the_sums_do_not_depend_on_the_schedule(fdm, precision):
         d = a.double()
         # compensated sums: a few units in the last place of the sum of the values' sizes
         assert abs(x[0] - float(d.sum().cpu())) <= 1e-13 * float(d.abs().sum().cpu()), (nx, ny)
+
+
+def test_captured_steps_keep_their_arrays(fdm):
+    """Steps of a batch captured by the caller, replayed after diagnostics of
+    other arrays (copies of the state, say): they still advance their own."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(3)
+    sizes = [(70, 50), (33, 90)]
+
+    def state():
+        return [torch.randn(ny, nx, device="cuda", generator=g) for nx, ny in sizes]
+    t11, t12 = state(), state()
+    r11, r12 = [t.clone() for t in t11], [t.clone() for t in t12]
+    c11, c12 = [t.clone() for t in t11], [t.clone() for t in t12]
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    descs = [fdm.desc(nx, ny) for nx, ny in sizes]
+    with torch.cuda.stream(s):
+        ctx = fdm.fdm_transport_init(descs, stream=s)
+        fdm.fdm_transport_step(ctx, t11, t12, 2)   # binds the arrays
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            fdm.fdm_transport_step(ctx, t11, t12, 2)
+        for k in range(3):
+            sums = fdm.fdm_transport_stats(ctx, c11, c12)
+            graph.replay()
+        own = fdm.fdm_transport_stats(ctx, t11, t12)
+    torch.cuda.synchronize()
+    fdm.fdm_destroy(ctx)
+    ctx = fdm.fdm_transport_init(descs)
+    first = [x["sum_abs"] for x in fdm.fdm_transport_stats(ctx, r11, r12)]
+    fdm.fdm_transport_step(ctx, r11, r12, 8)
+    last = [x["sum_abs"] for x in fdm.fdm_transport_stats(ctx, r11, r12)]
+    torch.cuda.synchronize()
+    fdm.fdm_destroy(ctx)
+    for x, y in zip(t11 + t12, r11 + r12):
+        assert torch.equal(x, y)
+    assert [x["sum_abs"] for x in sums] == first and [x["sum_abs"] for x in own] == last
