@@ -399,8 +399,10 @@ typedef struct fdm_tune_trial {
  * for each schedule that applies: batched and plain (several instances),
  * and fused (FP32 precision, time_order 2 or 3, semi-discrete scheme, or
  * wherever AUTO itself takes fused launches).  Each candidate is timed twice; the three fastest are then timed three more
- * times each, interleaved, and the context keeps the fastest of them.  alpha11/alpha12 are read, never
- * written; the step count and diagnostics baseline are unchanged.  Up to
+ * times each, interleaved, and the context keeps the fastest of them.  An FDM_SCHEDULE_AUTO context of one
+ * instance of one row takes the same launches in any tiling: one trial of
+ * them (of two steps at least), and the context stays as it is.
+ * alpha11/alpha12 are read, never written; the step count and diagnostics baseline are unchanged.  Up to
  * max_trials measured candidates are written to trials (may be NULL when
  * max_trials is 0) and their number to *n_trials (may be NULL).  Synchronous:
  * returns after the last trial.  Allocates the scratch copy (state size) for

@@ -222,10 +222,16 @@ fdm_status bind(fdm_ctx *c, void *const *a11, void *const *a12)
     return FDM_OK;
 }
 
+// Whether steps go by the one-row kernel, whatever the tiling (two or more).
+bool several_steps_a_launch(const fdm_ctx *c)
+{
+    return c->schedule == FDM_SCHEDULE_AUTO && c->n == 1 && c->desc[0].ny == 1;
+}
+
 // Enqueue n_steps on stream s for the bound arrays.
 fdm_status enqueue_steps(fdm_ctx *c, int32_t n_steps, hipStream_t s)
 {
-    if (c->schedule == FDM_SCHEDULE_AUTO && c->n == 1 && c->desc[0].ny == 1 && n_steps >= 2) {
+    if (several_steps_a_launch(c) && n_steps >= 2) {
         FDM_HIP(c, run_line_steps(c->inst[0], c->time_order, c->precision, n_steps, s));
         return FDM_OK;
     }
@@ -970,6 +976,10 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
     } else {
         schedules = {was_fused ? FDM_SCHEDULE_FUSED : was_batched ? FDM_SCHEDULE_BATCHED : FDM_SCHEDULE_PLAIN};
     }
+    // one row: the same launches whatever the tiling and schedule; one trial of
+    // them as the context is, and nothing to choose
+    const bool one_row = several_steps_a_launch(c);
+    if (one_row) schedules = {was_fused ? FDM_SCHEDULE_FUSED : FDM_SCHEDULE_PLAIN};
 
     // Seconds per step of one launch shape on the scratch state: a warm-up
     // step, then the fastest of `reps` timed runs of trial_steps steps.
@@ -984,7 +994,8 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
         if (r != FDM_OK) return r;
         double best_t = 0.0;
         // an odd fused count ends on the stage kernels: time an even one
-        const int32_t steps = trial_steps + (fused && trial_steps < INT32_MAX ? trial_steps & 1 : 0);
+        const int32_t steps =
+            one_row ? std::max(trial_steps, 2) : trial_steps + (fused && trial_steps < INT32_MAX ? trial_steps & 1 : 0);
         for (int k = 0; k < reps; ++k) {
             FDM_HIP(c, hipEventRecord(e0, c->stream));
             r = enqueue_steps(c, steps, c->stream);
@@ -1027,9 +1038,10 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
             // smallest height with at most k waves per SIMD (k = 1 .. 8)
             // evens the SIMDs out at the least halo work for k rounds.
             std::vector<int> heights;
+            if (one_row) heights = {c->inst[0].rows};
             for (int rows : {4, 8, 12, 16, 24, 32, 48, 64})
-                if (rows <= max_ny || rows == 4) heights.push_back(rows);
-            for (int k = 1; k <= 8; ++k) {
+                if (!one_row && (rows <= max_ny || rows == 4)) heights.push_back(rows);
+            for (int k = 1; k <= 8 && !one_row; ++k) {
                 const int rows = balanced_rows(c, fused, batched, max_ny, k * simds);
                 if (rows > 0 && rows <= kMaxBalancedRows &&
                     std::find(heights.begin(), heights.end(), rows) == heights.end())
@@ -1075,16 +1087,17 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
     if (e1) (void)hipEventDestroy(e1);
     (void)hipStreamSynchronize(c->stream);
     (void)hipFree(scratch);
-    if (st == FDM_OK && best_rows > 0) {
+    if (st == FDM_OK && best_rows > 0 && !one_row) {
         c->batched = best_batched;
         c->fused = best_fused;
         st = retile(c, best_rows);
         if (st == FDM_OK) c->requested_rows = best_rows;
     } else if (!c->sticky) {
-        // restore the previous tiling after a non-device failure
+        // the previous tiling: after a non-device failure, or with nothing to choose
         c->batched = was_batched;
         c->fused = was_fused;
-        (void)retile(c, c->requested_rows);
+        const fdm_status rs = retile(c, c->requested_rows);
+        if (st == FDM_OK) st = rs;
     }
     c->table_valid = false;   // the table points at the scratch arrays
     if (n_trials) *n_trials = std::min(count, max_trials);
