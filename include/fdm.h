@@ -395,11 +395,12 @@ typedef struct fdm_tune_trial {
  * smallest height (at most 512) whose largest launch has at most k waves
  * per SIMD of the device (a wave per tile; four SIMDs per compute unit),
  * so that the SIMDs carry equal work; and, for a context created with
- * FDM_SCHEDULE_AUTO,
- * for each schedule that applies: batched and plain (several instances),
- * and fused (FP32 precision, time_order 2 or 3, semi-discrete scheme, or
- * wherever AUTO itself takes fused launches).  Each candidate is timed twice; the three fastest are then timed three more
- * times each, interleaved, and the context keeps the fastest of them.  An FDM_SCHEDULE_AUTO context of one
+ * FDM_SCHEDULE_AUTO, for each schedule that applies: batched and plain
+ * (several instances), and fused (FP32 precision, time_order 2 or 3,
+ * semi-discrete scheme, or wherever AUTO itself takes fused launches; timed
+ * over the next number of steps that is fused launches alone, at most three
+ * more).  Each candidate is timed twice; the three fastest are then timed three
+ * more times each, interleaved, and the context keeps the fastest of them.  An FDM_SCHEDULE_AUTO context of one
  * instance of one row takes the same launches in any tiling: one trial of
  * them (of two steps at least), and the context stays as it is.
  * alpha11/alpha12 are read, never written; the step count and diagnostics baseline are unchanged.  Up to

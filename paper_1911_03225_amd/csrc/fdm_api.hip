@@ -993,9 +993,10 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
         r = enqueue_steps(c, 1, c->stream);
         if (r != FDM_OK) return r;
         double best_t = 0.0;
-        // an odd fused count ends on the stage kernels: time an even one
-        const int32_t steps =
-            one_row ? std::max(trial_steps, 2) : trial_steps + (fused && trial_steps < INT32_MAX ? trial_steps & 1 : 0);
+        // (fused: counts that are fused launches alone)
+        const int32_t steps = one_row ? std::max(trial_steps, 2)
+                              : fused ? fused_steps(c->time_order, trial_steps)
+                                      : trial_steps;
         for (int k = 0; k < reps; ++k) {
             FDM_HIP(c, hipEventRecord(e0, c->stream));
             r = enqueue_steps(c, steps, c->stream);
@@ -1104,9 +1105,19 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
     return st;
 }
 
-// Graph launches of the context's coupled runs so far.  For the tests alone:
-// not part of the interface, and not declared in fdm.h.
+// For the tests alone: not part of the interface, and not declared in fdm.h.
+// Graph launches of the context's coupled runs so far.
 int64_t fdm_test_coupled_replays(const fdm_ctx *c) { return c ? c->cw.replays : -1; }
+// How the autotuner's trial of the fused kernel is launched: its steps, and
+// the launches and single steps they take.
+int32_t fdm_test_fused_trial(int32_t order, int32_t trial_steps, int32_t *launches, int32_t *singles)
+{
+    const int32_t steps = fused_steps(order, trial_steps);
+    const FusedPlan plan = fused_plan(order, steps);
+    *launches = plan.fused;
+    *singles = plan.single;
+    return steps;
+}
 
 double fdm_transport_dt(const fdm_ctx *c, int32_t i)
 {

@@ -83,9 +83,20 @@ int64_t strip_rows_of(const fdm_transport_desc &d);
 // 2 Heun, 3 explicit midpoint): the modes in order, their count returned.
 int stage_modes(int32_t order, int32_t step, int modes[2]);
 
-// n_steps of one instance by the fused kernel (order 2 or 3, float32), whose
-// launches go from the state to the stage buffer and back; the last of an odd
-// count by the stage kernels, in place.  rows: the tile height asked for, or 0.
+// How n_steps of one instance are launched when it takes the fused kernel:
+// `fused` launches from the state to the stage buffer and back, then `single`
+// steps by the stage kernels.  The launches end in the state, unless the one
+// step of a single-stage integrator is all there is.
+struct FusedPlan {
+    int32_t fused, single;
+};
+FusedPlan fused_plan(int32_t order, int32_t n_steps);
+
+// The fewest steps, not below n, that are fused launches alone (n itself where
+// that would pass the largest number of steps).
+int32_t fused_steps(int32_t order, int32_t n);
+
+// n_steps of one instance by that plan.  rows: the tile height asked for, or 0.
 hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds, int32_t order,
                            int32_t precision, int32_t n_steps, hipStream_t s);
 

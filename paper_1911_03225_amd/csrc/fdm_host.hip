@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
+#include <climits>
 #include <cstdio>
 #include <cstring>
 
@@ -319,35 +320,40 @@ int stage_modes(int32_t order, int32_t step, int modes[2])
 // One stage a step (float): a fused launch takes two steps, and single steps
 // (in either direction) fill up so that the last launch writes the state: an
 // odd number of fused launches and then single ones back, or an even number.
+FusedPlan fused_plan(int32_t order, int32_t n_steps)
+{
+    if (order != 1) return {n_steps - (n_steps & 1), n_steps & 1};
+    // n mod 4: 0, pairs alone; 1, three singles; 2, two singles; 3, one
+    const int32_t single = n_steps == 1 ? 1 : n_steps % 4 == 0 ? 0 : 4 - n_steps % 4;
+    return {(n_steps - single) / 2, single};
+}
+
+int32_t fused_steps(int32_t order, int32_t n)
+{
+    const int32_t whole = order == 1 ? 4 : 2, up = (whole - n % whole) % whole;
+    return n > INT32_MAX - up ? n : n + up;
+}
+
 hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds, int32_t order,
                            int32_t precision, int32_t n_steps, hipStream_t s)
 {
     InstDev J = I;
     if (rows <= 0) J.rows = launch_rows(J.strips, d.ny, stage_rows_of(d, simds));
     J.chunks = tiles_along_y(d.ny, J.rows);
+    const FusedPlan plan = fused_plan(order, n_steps);
+    const int integ = order == 1 ? FUSED_TWO_STEPS : order == 3 ? FUSED_MIDPOINT : FUSED_HEUN;
     hipError_t e = hipSuccess;
-    if (order == 1) {
-        // n mod 4: 0, pairs alone; 1, three singles; 2, two singles; 3, one
-        const int32_t singles = n_steps == 1 ? 1 : n_steps % 4 == 0 ? 0 : 4 - n_steps % 4;
-        const int32_t pairs = (n_steps - singles) / 2;
-        for (int32_t k = 0; k < pairs && e == hipSuccess; ++k) e = launch_fused(I, k & 1, FUSED_TWO_STEPS, precision, s);
-        for (int32_t k = 0; k < singles && e == hipSuccess; ++k)
-            e = launch_stage(J, (pairs + k) & 1 ? MODE_BWD : MODE_FWD, precision, s);
-        if (n_steps == 1) {
-            const int64_t n = (int64_t)I.nx * I.ny;
-            if (e == hipSuccess) e = launch_copy(I.a11, I.w11, n, precision, s);
-            if (e == hipSuccess) e = launch_copy(I.a12, I.w12, n, precision, s);
-        }
-        return e;
+    for (int32_t k = 0; k < plan.fused && e == hipSuccess; ++k) e = launch_fused(I, k & 1, integ, precision, s);
+    for (int32_t k = 0; k < plan.single && e == hipSuccess; ++k) {
+        int modes[2];
+        const int nm = stage_modes(order, plan.fused + k, modes);
+        for (int m = 0; m < nm && e == hipSuccess; ++m) e = launch_stage(J, modes[m], precision, s);
     }
-    const int integ = order == 3 ? FUSED_MIDPOINT : FUSED_HEUN;
-    for (int32_t step = 0; step + 1 < n_steps; step += 2)
-        for (int dir = 0; dir < 2; ++dir)
-            if ((e = launch_fused(I, dir, integ, precision, s)) != hipSuccess) return e;
-    if (!(n_steps & 1)) return hipSuccess;
-    int modes[2];
-    const int nm = stage_modes(order, 0, modes);
-    for (int m = 0; m < nm && e == hipSuccess; ++m) e = launch_stage(J, modes[m], precision, s);
+    if (order == 1 && n_steps == 1) {
+        const int64_t n = (int64_t)I.nx * I.ny;
+        if (e == hipSuccess) e = launch_copy(I.a11, I.w11, n, precision, s);
+        if (e == hipSuccess) e = launch_copy(I.a12, I.w12, n, precision, s);
+    }
     return e;
 }
 
