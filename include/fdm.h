@@ -146,9 +146,10 @@ typedef enum fdm_schedule {
                                   one row, several steps a launch; one fused
                                   launch per step (FP32: wherever FUSED applies;
                                   one instance in the FP64 modes: beyond the
-                                  on-chip cache); for one FP32 instance with
-                                  single-stage steps, two of them in a fused
-                                  launch (FULLY_DISCRETE: up to 2^20 nodes); else
+                                  on-chip cache; a batch: up to 2^25 tiles);
+                                  for one FP32 instance with single-stage
+                                  steps, two of them in a fused launch
+                                  (FULLY_DISCRETE: up to 2^20 nodes); else
                                   batched launches when n_instances > 1, else
                                   plain                                        */
     FDM_SCHEDULE_BATCHED = 1,  /* one launch per stage for all instances       */

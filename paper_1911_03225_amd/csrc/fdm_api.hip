@@ -801,7 +801,13 @@ fdm_status fdm_transport_init(const fdm_transport_desc *descs, int32_t n_instanc
     c->dt_last = c->dt;
     {
         c->requested_rows = opt.tile_rows;
-        const fdm_status ts = retile(c, opt.tile_rows);
+        fdm_status ts = retile(c, opt.tile_rows);
+        if (ts == FDM_ERR_INVALID_ARG && c->fused && opt.schedule == FDM_SCHEDULE_AUTO) {
+            // more fused tiles (56 columns) than a launch takes: the stage kernels' (60) may fit
+            c->fused = false;
+            c->err.clear();
+            ts = retile(c, opt.tile_rows);
+        }
         if (ts != FDM_OK) return bail(ts);
     }
     INIT_HIP(hipStreamCreateWithFlags(&c->capture, hipStreamNonBlocking));
