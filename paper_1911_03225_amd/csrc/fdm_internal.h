@@ -255,10 +255,6 @@ hipError_t launch_fused_batched(const InstDev *d_inst, const int32_t *d_tile_ins
 // scheme and precision.
 int line_steps(int order);
 hipError_t launch_line(const InstDev &I, int order, int steps, int dir, int precision, hipStream_t s);
-// After an odd number of batched fused steps: the stage buffers of every
-// instance back into the states, over the same tile map.
-hipError_t launch_copy_back_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles,
-                                    hipStream_t s);
 // out: five doubles (pinned host memory: the kernels write them there).
 hipError_t launch_stats(const void *a11, const void *a12, int64_t n, int precision,
                         StatsPartial *d_partials, double *out, hipStream_t s);

@@ -48,41 +48,6 @@ hipError_t launch_fused_batched(const InstDev *d_inst, const int32_t *d_tile_ins
     return hipGetLastError();
 }
 
-namespace {
-// One wave per fused tile: its 56 columns by `rows` rows of both components
-// from the stage buffer to the state (bound by memory; one launch for all
-// instances instead of two per instance).
-__global__ __launch_bounds__(kBlock) void copy_back_kernel(const InstDev *__restrict__ insts,
-                                                           const int32_t *__restrict__ tile_inst,
-                                                           int64_t total_tiles, int blocks_per_xcd)
-{
-    const int64_t tile = xcd_tile(blocks_per_xcd);
-    if (tile >= total_tiles) return;
-    const InstDev I = insts[tile_inst[tile]];
-    const int local = (int)(tile - I.tile_begin);
-    const int col = local % I.fstrips * kFStrip + (int)(threadIdx.x & 63), k0 = local / I.fstrips * I.rows;
-    if ((int)(threadIdx.x & 63) >= kFStrip || col >= I.nx) return;
-    const int nrows = min(I.rows, I.ny - k0);
-    const float *s11 = static_cast<const float *>(I.w11), *s12 = static_cast<const float *>(I.w12);
-    float *d11 = static_cast<float *>(I.a11), *d12 = static_cast<float *>(I.a12);
-    for (int r = 0; r < nrows; ++r) {
-        const size_t at = (size_t)(k0 + r) * (size_t)I.nx + (size_t)col;
-        d11[at] = s11[at];
-        d12[at] = s12[at];
-    }
-}
-}  // namespace
-
-hipError_t launch_copy_back_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles,
-                                    hipStream_t s)
-{
-    const int64_t blocks = (total_tiles + kWavesPerBlock - 1) / kWavesPerBlock;
-    const int per_xcd = (int)((blocks + 7) / 8);
-    hipLaunchKernelGGL(copy_back_kernel, dim3(8 * per_xcd), dim3(kBlock), 0, s, d_inst, d_tile_inst, total_tiles,
-                       per_xcd);
-    return hipGetLastError();
-}
-
 hipError_t launch_stage_batched_f32(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles,
                                     int mode, bool fd, hipStream_t s)
 {
