@@ -43,7 +43,7 @@ struct fdm_ctx {
     InstDev *h_inst_pinned = nullptr;       // staging for table uploads
     int32_t *d_tile_inst = nullptr;         // batched: tile -> instance, then (fused) those of odd_inst
     int64_t total_tiles = 0;
-    std::vector<InstDev> odd_inst;          // batched and fused: the views in the stage kernels' tiling
+    std::vector<InstDev> odd_inst;          // fused: the views in the stage kernels' tiling
     int64_t odd_tiles = 0;
     fdm::StatsPartial *d_partials = nullptr;
     double *h_stats = nullptr;              // 5 doubles per instance, pinned (the kernels write them)
@@ -213,15 +213,15 @@ fdm_status bind(fdm_ctx *c, void *const *a11, void *const *a12)
         c->inst[i].a11 = a11[i];
         c->inst[i].a12 = a12[i];
     }
+    for (size_t i = 0; i < c->odd_inst.size(); ++i) {
+        c->odd_inst[i].a11 = a11[i];
+        c->odd_inst[i].a12 = a12[i];
+    }
     if (c->batched && changed) {
         // the staging buffer may still feed an earlier upload
         FDM_HIP(c, hipStreamSynchronize(c->stream));
         std::memcpy(c->h_inst_pinned, c->inst.data(), sizeof(InstDev) * c->n);
-        for (size_t i = 0; i < c->odd_inst.size(); ++i) {
-            c->odd_inst[i].a11 = a11[i];
-            c->odd_inst[i].a12 = a12[i];
-            c->h_inst_pinned[c->n + i] = c->odd_inst[i];
-        }
+        for (size_t i = 0; i < c->odd_inst.size(); ++i) c->h_inst_pinned[c->n + i] = c->odd_inst[i];
         FDM_HIP(c, hipMemcpyAsync(c->d_inst, c->h_inst_pinned, sizeof(InstDev) * (c->n + c->odd_inst.size()),
                                   hipMemcpyHostToDevice, c->stream));
     }
@@ -244,8 +244,7 @@ fdm_status enqueue_steps(fdm_ctx *c, int32_t n_steps, hipStream_t s)
     }
     if (c->fused && !c->batched) {
         for (int i = 0; i < c->n; ++i)
-            FDM_HIP(c, run_fused_steps(c->inst[i], c->desc[i], c->requested_rows, c->simds, c->time_order,
-                                       c->precision, n_steps, s));
+            FDM_HIP(c, run_fused_steps(c->inst[i], c->odd_inst[i], c->time_order, c->precision, n_steps, s));
         return FDM_OK;
     }
     if (c->fused) {
@@ -339,12 +338,16 @@ fdm_status retile(fdm_ctx *c, const int asked)
         FDM_HIP(c, hipGraphExecDestroy(c->graph));
         c->graph = nullptr;
     }
-    if (!c->batched) return FDM_OK;
+    c->odd_inst.clear();
+    c->odd_tiles = 0;
+    if (!c->batched) {
+        for (int i = 0; c->fused && i < c->n; ++i)
+            c->odd_inst.push_back(stage_tiling(c->inst[i], c->desc[i], asked, c->simds));
+        return FDM_OK;
+    }
     if (tile > kMaxLaunchTiles) return fail(c, FDM_ERR_INVALID_ARG, "too many tiles for one batched launch");
     // the same instances in the stage kernels' tiling (fewer strips, so the
     // fused launch's heights fit where their own do not)
-    c->odd_inst.clear();
-    c->odd_tiles = 0;
     if (c->fused) {
         c->odd_inst = c->inst;
         const bool fits = launch_waves(c, false, true, odd) <= kMaxLaunchTiles;

@@ -96,9 +96,14 @@ FusedPlan fused_plan(int32_t order, int32_t n_steps);
 // that would pass the largest number of steps).
 int32_t fused_steps(int32_t order, int32_t n);
 
-// n_steps of one instance by that plan.  rows: the tile height asked for, or 0.
-hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds, int32_t order,
-                           int32_t precision, int32_t n_steps, hipStream_t s);
+// n_steps of one instance by that plan.  odd: the instance in the stage
+// kernels' tiling, for the single steps.
+hipError_t run_fused_steps(const InstDev &I, const InstDev &odd, int32_t order, int32_t precision, int32_t n_steps,
+                           hipStream_t s);
+
+// The instance in the stage kernels' tiling with `rows` rows a tile, or the
+// default where that is 0.
+InstDev stage_tiling(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds);
 
 // n_steps >= 2 of a one-row instance by launches of several steps each, an
 // even number of them (the last writes the state).

@@ -334,12 +334,17 @@ int32_t fused_steps(int32_t order, int32_t n)
     return n > INT32_MAX - up ? n : n + up;
 }
 
-hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds, int32_t order,
-                           int32_t precision, int32_t n_steps, hipStream_t s)
+InstDev stage_tiling(const InstDev &I, const fdm_transport_desc &d, int rows, int64_t simds)
 {
     InstDev J = I;
     if (rows <= 0) J.rows = launch_rows(J.strips, d.ny, stage_rows_of(d, simds));
     J.chunks = tiles_along_y(d.ny, J.rows);
+    return J;
+}
+
+hipError_t run_fused_steps(const InstDev &I, const InstDev &odd, int32_t order, int32_t precision, int32_t n_steps,
+                           hipStream_t s)
+{
     const FusedPlan plan = fused_plan(order, n_steps);
     const int integ = order == 1 ? FUSED_TWO_STEPS : order == 3 ? FUSED_MIDPOINT : FUSED_HEUN;
     hipError_t e = hipSuccess;
@@ -347,7 +352,7 @@ hipError_t run_fused_steps(const InstDev &I, const fdm_transport_desc &d, int ro
     for (int32_t k = 0; k < plan.single && e == hipSuccess; ++k) {
         int modes[2];
         const int nm = stage_modes(order, plan.fused + k, modes);
-        for (int m = 0; m < nm && e == hipSuccess; ++m) e = launch_stage(J, modes[m], precision, s);
+        for (int m = 0; m < nm && e == hipSuccess; ++m) e = launch_stage(odd, modes[m], precision, s);
     }
     if (order == 1 && n_steps == 1) {
         const int64_t n = (int64_t)I.nx * I.ny;

@@ -131,21 +131,24 @@ extern "C" fdm_status fdm_transport_step_noalloc(const fdm_transport_desc *desc,
     fill_inst(I, d, step_dt(d, smax), stage, stage + (size_t)n * sizeof(float));
     I.a11 = alpha11;
     I.a12 = alpha12;
-    I.rows = stage_rows_of(d, simds);
     I.strips = (d.nx + fdm::kStrip - 1) / fdm::kStrip;
     I.fstrips = (d.nx + fdm::kFusedStrip - 1) / fdm::kFusedStrip;
-    I.chunks = fdm::tiles_along_y(d.ny, I.rows);
     if (d.ny == 1 && n_steps >= 2) {
         e = run_line_steps(I, order, FDM_PRECISION_FP32, n_steps, s);
         return e == hipSuccess ? FDM_OK : device_error("line launch", e);
     }
     if (fused_by_default(&d, 1, FDM_PRECISION_FP32, order)) {
-        I.rows = fused_rows([&](int h) { return (int64_t)I.fstrips * fdm::tiles_along_y(d.ny, h); }, d.ny, simds);
-        I.chunks = fdm::tiles_along_y(d.ny, I.rows);
-        e = run_fused_steps(I, d, 0, simds, order, FDM_PRECISION_FP32, n_steps, s);
+        const FusedPlan plan = fused_plan(order, n_steps);   // only the tilings it needs
+        const InstDev odd = plan.single > 0 ? stage_tiling(I, d, 0, simds) : I;
+        if (plan.fused > 0) {
+            I.rows = fused_rows([&](int h) { return (int64_t)I.fstrips * fdm::tiles_along_y(d.ny, h); }, d.ny, simds);
+            I.chunks = fdm::tiles_along_y(d.ny, I.rows);
+        }
+        e = run_fused_steps(I, odd, order, FDM_PRECISION_FP32, n_steps, s);
         return e == hipSuccess ? FDM_OK : device_error("fused launch", e);
     }
     // large fully discrete grids: a launch a step, to and from the stage buffer
+    I = stage_tiling(I, d, 0, simds);
     for (int32_t step = 0; step < n_steps; ++step)
         if ((e = fdm::launch_stage(I, step & 1 ? fdm::MODE_BWD : fdm::MODE_FWD, fdm::PREC_FP32, s)) != hipSuccess)
             return device_error("stage launch", e);
