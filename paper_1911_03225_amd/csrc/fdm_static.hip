@@ -577,7 +577,10 @@ const char *rocfft_message(rocfft_status s)
 // Whether the own transforms take a plan whose lines fit.
 //   A single solve: rocFFT builds two plans for it, 5 to 14 ms; three kernels
 // and their tables take 45 to 150 us up to 1024^2, 0.6 ms where a line's
-// length is a prime (direct sums, whose number the bound keeps at a few ms).
+// length is a prime.  There, two bounds: on all the direct sums (1021^2 3.4 ms
+// against 20), and on those of a line, which one block does: float, 13 x 2503
+// 6.0 ms against 12.4, 13 x 3001 11.0 / 13.4, but 13 x 3511 15.1 / 12.2 and
+// 13 x 4099 28 / 11.4 (double lines of that length do not fit).
 //   A coupled run pays for its plan once.  In double: 512^2 48 us a step
 // against rocFFT's 67, 1024^2 122 / 137, 2048^2 315 / 366, 448^2 (a factor 7)
 // 66 / 76, 496^2 (31) 106 / 151; primes of 11 to 17 are among rocFFT's radices
@@ -587,8 +590,10 @@ const char *rocfft_message(rocfft_status s)
 // what it gave before: float keeps rocFFT.
 bool own_transforms(const StaticParams &q, bool once)
 {
-    const int p = std::max(largest_prime(q.nx), largest_prime(q.ny));
-    if (once) return (int64_t)q.nx * q.ny * p <= (int64_t)1 << 30;
+    const int px = largest_prime(q.nx), py = largest_prime(q.ny), p = std::max(px, py);
+    if (once)
+        return (int64_t)q.nx * q.ny * p <= (int64_t)1 << 30 &&
+               std::max((int64_t)q.nx * px, (int64_t)q.ny * py) <= (int64_t)1 << 23;
     return q.f64 && (p <= 7 || (p > 17 && p <= 31));
 }
 
