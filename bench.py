@@ -250,9 +250,8 @@ def single_instance(fdm, a11, a12, K, W, repeats, stream, desc_kw, options, auto
     ctx = fdm.fdm_transport_init(fdm.desc(nx, ny, v0_field=field, **desc_kw), options=options, stream=stream,
                                  keep=[field] if field is not None else [])
     sched = options.get("schedule", "auto")
-    if sched == "auto":   # the library's own choice for one instance of these legs, when not tuned
-        two_stage = desc_kw.get("scheme", "semidiscrete") == "semidiscrete" and desc_kw.get("time_order") in (None, 0, 2, 3)
-        sched = "fused" if two_stage and options.get("precision", "fp32") == "fp32" else "plain"
+    if sched == "auto":   # the library's own choice, when not tuned
+        sched = "fused" if fdm.load_library().fdm_debug_fused(ctx.handle) else "plain"
     trials, choice = None, "fixed" if options.get("tile_rows") else "default rule"
     if autotune:
         trials = fdm.fdm_autotune(ctx, [t11], [t12], trial_steps=20)

@@ -531,8 +531,8 @@ fdm_status coupled_run(fdm_ctx *c, const fdm_loading &L, void *const *a11, void 
 
     // The step scalars live on the device: each step enqueues its kernels
     // without waiting (the step size by the stage kernels, the mean slip and
-    // stress by the next step's pack kernel or, at a chunk end, one block);
-    // the host reads them back once per chunk.
+    // stress by a block of the next step's solve or, at the end of a run of
+    // steps, by a kernel of one block); the host reads them back once per chunk.
     const double h = std::min(d.dx, d.dy), mu = L.mu, frac = (double)q.h / (double)q.n3;
     FDM_HIP(c, hipStreamSynchronize(c->stream));   // the pinned mirror may feed an earlier copy
     std::memset(w.h_cd, 0, sizeof(fdm::CoupledDev));
@@ -1150,12 +1150,15 @@ fdm_status fdm_autotune(fdm_ctx *c, void *const *alpha11, void *const *alpha12, 
     return st;
 }
 
-// For the tests alone: not part of the interface, and not declared in fdm.h.
+// For the tests and the benchmark's labels alone: not part of the interface,
+// and not declared in fdm.h.
+// Whether the context takes fused launches.
+int32_t fdm_debug_fused(const fdm_ctx *c) { return c && c->fused; }
 // Graph launches of the context's coupled runs so far.
-int64_t fdm_test_coupled_replays(const fdm_ctx *c) { return c ? c->cw.replays : -1; }
+int64_t fdm_debug_coupled_replays(const fdm_ctx *c) { return c ? c->cw.replays : -1; }
 // How the autotuner's trial of the fused kernel is launched: its steps, and
 // the launches and single steps they take.
-int32_t fdm_test_fused_trial(int32_t order, int32_t trial_steps, int32_t *launches, int32_t *singles)
+int32_t fdm_debug_fused_trial(int32_t order, int32_t trial_steps, int32_t *launches, int32_t *singles)
 {
     const int32_t steps = fused_steps(order, trial_steps);
     const FusedPlan plan = fused_plan(order, steps);

@@ -242,12 +242,12 @@ hipError_t launch_absmax(const float *v, int64_t n, float *d_partial, hipStream_
 // explicit midpoint step, or two steps of a single-stage integrator.
 enum : int { FUSED_HEUN = 0, FUSED_MIDPOINT = 1, FUSED_TWO_STEPS = 2 };
 
-// Fused two-stage step of one instance (semi-discrete scheme; Heun, or the explicit midpoint when mid): dir 0 from
-// the state into the stage buffer, dir 1 back; tiles of I.rows rows and 56
-// columns.
+// A fused launch of one instance (integ: FUSED_*; the FP64 modes take Heun and
+// midpoint steps only): dir 0 from the state into the stage buffer, dir 1
+// back; tiles of I.rows rows and 56 columns.
 hipError_t launch_fused(const InstDev &I, int dir, int integ, int precision, hipStream_t s);
-// The same for every instance of a batched context in one launch (the tile
-// map and tile_begin of the fused tiling).
+// A Heun step (midpoint: mid) of every instance of a batched context in one
+// launch (the tile map and tile_begin of the fused tiling), float.
 hipError_t launch_fused_batched(const InstDev *d_inst, const int32_t *d_tile_inst, int64_t total_tiles, int dir,
                                 bool mid, hipStream_t s);
 // `steps` (at most line_steps) time steps of a one-row instance in one

@@ -7,7 +7,7 @@ from paper_1911_03225_amd import fdm
 
 
 def _trial(order, steps):
-    f = fdm.load_library().fdm_test_fused_trial   # (exported for this test)
+    f = fdm.load_library().fdm_debug_fused_trial   # (exported for this test)
     f.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
     f.restype = ctypes.c_int32
     launches, singles = ctypes.c_int32(), ctypes.c_int32()

@@ -29,7 +29,7 @@ def _case(nx=72, ny=56):
 
 
 def _replays(fdm, ctx):
-    f = fdm.load_library().fdm_test_coupled_replays   # (the library's counter for this test)
+    f = fdm.load_library().fdm_debug_coupled_replays   # (the library's counter for this test)
     f.argtypes, f.restype = [ctypes.c_void_p], ctypes.c_int64
     return f(ctx.handle)
 
