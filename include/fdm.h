@@ -316,8 +316,9 @@ fdm_status fdm_static_solve(const fdm_static_desc *desc, const void *alpha11,
  *      FDM_LAW_WIGGLY: v0 = m (tau_y cos(U^p_13 / beta) - tau13), the wiggly
  *        energy G = beta sin(U^p_13/beta) tau_y of sec. 3.2.1 (eq. 56 form),
  *        with U^p_13 = phi at the nodes recovered by the static solve's
- *        transforms (one more inverse FFT per step).  float32 cannot resolve
- *        phi / beta for the paper's beta = 1e-8: use FDM_PRECISION_FP64;
+ *        transforms (one more inverse FFT per step, or the second half of one
+ *        complex transform).  float32 cannot resolve phi / beta for the
+ *        paper's beta = 1e-8: use FDM_PRECISION_FP64;
  *      v0 < 0 moves fronts so as to raise U^p_13 where the stress exceeds the
  *      friction;
  *   3. dt = the largest float <= min(cfl min(dx,dy) / max|v0|, dt_max)
@@ -361,10 +362,10 @@ typedef struct fdm_loading {
  * descriptor) and dx == dy; the descriptor's v0 / v0_field are not used
  * during the run (they are again after it).  The step size, mean slip and
  * mean stress are computed on the device, so steps are enqueued without
- * waiting; a call of 160 steps or more whose chunks hold at least 16 replays
- * them from a HIP graph of 16 steps captured once per call (where the
- * launches can be captured as kernels; otherwise, and for what is left of a
- * chunk, the same kernels are enqueued directly), and the stream is
+ * waiting; calls long enough to earn the capture back replay them from a HIP
+ * graph of at most 16 steps, an equal share of a chunk, captured once per call
+ * (where the launches can be captured as kernels; otherwise, and for what is
+ * left of a chunk, the same kernels are enqueued directly), and the stream is
  * synchronized once per chunk (for those scalars and the stats record).
  * Results do not depend on the chunk length.  The first call allocates the
  * coupled workspace (transform tables or FFT plans, spectra, a stress and a
